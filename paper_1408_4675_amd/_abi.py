@@ -48,7 +48,7 @@ KW_FIELD_RHOZ = 7
 EXPORTS = ("kw_workspace_size", "kw_create", "kw_prepare", "kw_plan_workspace_size",
            "kw_create_prepared", "kw_plan_destroy", "kw_create_static", "kw_step", "kw_gather", "kw_gather_bytes",
            "kw_set_field", "kw_gather_field", "kw_profile", "kw_stats", "kw_set_graph",
-           "kw_set_plan", "kw_state_bytes", "kw_save", "kw_load", "kw_adjoint_workspace_size",
+           "kw_set_plan", "kw_suggest_plan", "kw_state_bytes", "kw_save", "kw_load", "kw_adjoint_workspace_size",
            "kw_adjoint_create", "kw_adjoint_objective", "kw_adjoint_step", "kw_adjoint_source_gradient",
            "kw_adjoint_record_bytes", "kw_adjoint_record", "kw_adjoint_step_record",
            "kw_adjoint_gradient", "kw_adjoint_destroy", "kw_destroy", "kw_last_error")
@@ -156,6 +156,8 @@ def _load(path):
     lib.kw_set_graph.argtypes = [C.c_void_p, C.c_int32]
     lib.kw_set_plan.restype = C.c_int
     lib.kw_set_plan.argtypes = [C.c_void_p, C.c_int, P(C.c_int32), C.c_int32, C.c_int32]
+    lib.kw_suggest_plan.restype = C.c_int
+    lib.kw_suggest_plan.argtypes = lib.kw_set_plan.argtypes
     lib.kw_state_bytes.restype = C.c_int64
     lib.kw_state_bytes.argtypes = [C.c_void_p]
     lib.kw_save.restype = C.c_int

@@ -4,8 +4,9 @@ For each axis of a grid it times candidate radix schedules (and, for the
 column passes, column-tile widths; for the x rows, rows per block) with the
 library's per-kernel HIP-event profiling, keeps the fastest, and caches the
 choice as JSON keyed by device architecture, axis kind and transform length.
-`Simulation` applies cached choices automatically; without a cache the
-library's built-in defaults are used.  This plays the role that FFT planning
+`Simulation` applies cached choices automatically, to the passes that run on
+the radix-pass engines (the passes on staged transforms have schedules of their
+own); without a cache the library's built-in defaults are used.  This plays the role that FFT planning
 by measurement plays in the paper's cluster code (Section 3.4), but the search
 space is this library's own: radix factorisations 2/3/4/5/8/16(/32) and tile
 shapes of the LDS-staged passes.

@@ -260,6 +260,92 @@ bool axis_plan(int n, int axis, const std::vector<int> *rad, int &eng, FftPlan &
     return true;
 }
 
+// Stages of a column of the staged transforms (staged.h): the fewest stages, then
+// the smallest largest radix, of radices the kernels are built for (kPow2Y,
+// kAnyY).  At least two, one at each end of the column; the first has radix 1
+// where the length is a radix itself.
+bool stage_axis(int n, bool pow2, StageAxis &A) {
+    std::vector<int> last = {16, 8, 4, 2};
+    if (!pow2) last = {16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2};
+    std::vector<int> first = last;
+    first.push_back(1);
+    int best[3] = {0, 0, 0}, best_np = 4, best_max = INT_MAX;
+    auto take = [&](int np, int a, int b, int c) {
+        const int mx = std::max(a, std::max(b, c));
+        if (np > best_np || (np == best_np && mx >= best_max)) return;
+        best_np = np;
+        best_max = mx;
+        best[0] = a;
+        best[1] = b;
+        best[2] = c;
+    };
+    for (int c : last) {
+        if (n % c) continue;
+        const int m = n / c;
+        for (int a : first) {
+            if (m == a) take(2, a, c, 0);
+            if (a == 1 || m % a) continue;
+            for (int b : first)
+                if (b > 1 && a * b == m) take(3, a, b, c);
+        }
+    }
+    if (best_np > 3) return false;
+    A = StageAxis{};
+    A.n = n;
+    A.np = best_np;
+    int w = 1;
+    for (int p = 0; p < 3; ++p) {
+        A.r[p] = p < best_np ? best[p] : 1;
+        A.w[p] = w;
+        w *= A.r[p];
+    }
+    A.dw1 = FastDiv(A.w[1]);
+    A.d1 = FastDiv(A.r[1]);
+    A.d2 = FastDiv(A.r[2]);
+    return true;
+}
+
+int stage_rmax(const StageAxis &A) { return std::max(A.r[0], std::max(A.r[1], A.r[2])); }
+
+// Whether the z pass runs on staged transforms, and its tiles
+void pick_zstaged(const GridDev &g, double kx_max, double ky_max, double kz_max, size_t max_lds,
+                  LaunchCfg &c) {
+    const int n = g.nz;
+    c.zs = 0;
+    const bool pow2 = is_pow2(n);
+    if (!stage_axis(n, pow2, c.zs_axis)) return;
+    // The fixed-width engines keep the gradient and the merged absorption of 256
+    // and 1024 points, lengths that their 16- and 32-wide threads transform in
+    // two passes (gradient at 1024: three, in 4-column tiles).  Staged against
+    // fixed, us a launch: gradient 256^3 77 : 74, 128 x 128 x 512 49 : 63,
+    // 1024^3 10800 : 9700; merged absorption 256^3 103 : 88, 128 x 128 x 512
+    // 60 : 71, 1024^3 11400 : 7800; divergence 256^3 95 : 99, 128 x 128 x 512
+    // 56 : 74, 1024^3 11600 : 12500
+    c.zs_skip = n == 256 || n == 1024 ? 1u << ZM_GRAD | 1u << ZM_ABSM : 0u;
+    // kappa as a polynomial at every wavenumber of the grid
+    const double k2 = kx_max * kx_max + ky_max * ky_max + kz_max * kz_max;
+    if ((double)g.half_cdt * g.half_cdt * k2 > kKappaPolyMax) return;
+    if ((uint64_t)(n / c.zs_axis.r[0]) * g.M * g.ny * 8 + 256 >= (1ull << 32)) return;
+    // columns a tile: 16 (a 128-byte line) while two blocks fit a CU; 8 where
+    // 16 would leave the chip short of blocks
+    auto lds = [&](int tb, int tiles) { return 8 * ((size_t)2 * n + (size_t)tiles * n * tb); };
+    auto tile = [&](int tiles, int outs) {
+        int tb = 16;
+        while (tb > 1 && lds(tb, tiles) > 80 * 1024) tb /= 2;
+        while (tb > 8 && ((g.M + tb - 1) / tb) * g.ny * outs < 1024) tb /= 2;
+        return tb;
+    };
+    c.zs_tb = tile(1, 2);
+    c.zs_tb_absm = tile(2, 1);
+    c.zs_tb_grad = tile(3, 1);
+    c.zs_grad3 = c.zs_tb_grad >= 8;
+    if (!c.zs_grad3) c.zs_tb_grad = c.zs_tb;
+    if (lds(c.zs_tb, 1) > max_lds || lds(c.zs_tb_absm, 2) > max_lds) return;
+    // about one task a thread in the stage of the largest radix
+    c.zs_threads = std::min(512, std::max(64, (n * c.zs_tb / stage_rmax(c.zs_axis) + 63) / 64 * 64));
+    c.zs = pow2 ? 1 : 2;
+}
+
 // ---------------------------------------------------------------------------
 // workspace layout
 // ---------------------------------------------------------------------------
@@ -534,6 +620,8 @@ struct kw_sim {
     std::vector<Rec> recs;
     std::vector<hipEvent_t> pool;
     size_t max_lds = 64 * 1024;        // LDS bytes a block may use on this device
+    bool ys_off = false;            // the caller chose x or y schedules (kw_set_plan)
+    bool zs_off = false;               // and the z schedule
     bool merged_abs = false;           // absorption terms merged (scalar c0^2 tau, c0^2 eta)
     bool rho0_sum_in_z = false;        // absorbing with a constant rho0: the divergence
                                        // pass forms the spectrum of rho0 sum du
@@ -638,6 +726,8 @@ hipError_t enqueue_step(kw_sim *s) {
     float2 *s123[3] = {S[1], S[2], S[3]};
     float2 *s456[3] = {S[4], S[5], S[6]};
     float *const *rec = s->rec[0] ? s->rec : nullptr;
+    // with fused plane passes the launches of the y passes around an x pass
+    // drop out (the x pass's launcher runs them), and with them their traffic
     KW_L(KC_YFWD, 2, launch_ypass(st, g, c, t, s0, 1, false, &s->counters, &s->src, &s->sen));
     KW_L(KC_ZGRAD, 4, launch_zfused(st, g, c, t, ZM_GRAD, s0, s123));
     KW_L(KC_YINV, 6, launch_ypass(st, g, c, t, s123, 3, true, nullptr, nullptr));
@@ -833,6 +923,8 @@ int pick_tiles(kw_sim *s, int tile_y, int tile_z) {
             c.tb_za = 16;
         }
     }
+    pick_zstaged(g, kPi / s->grid.dx, kPi / s->grid.dy, kPi / s->grid.dz, s->max_lds, c);
+    if (s->zs_off) c.zs = 0;
     // the column passes address an element of their tile by a 32-bit byte offset
     const uint64_t zlane = ((uint64_t)std::max(c.pz.L, c.pza.L) * g.M * g.ny + std::max(c.tb_z, c.tb_za)) * 8;
     if (zlane >= (1ull << 32))
@@ -1587,18 +1679,24 @@ int kw_set_graph(kw_sim *s, int32_t steps_per_graph) {
     return KW_OK;
 }
 
-int kw_set_plan(kw_sim *s, int axis, const int32_t *radices, int32_t n_radices, int32_t tile) {
+static int apply_plan(kw_sim *s, int axis, const int32_t *radices, int32_t n_radices, int32_t tile,
+                      bool hint) {
     if (!s) return fail(KW_EINVAL, "sim is NULL");
     if (axis < 0 || axis > 2) return fail(KW_EINVAL, "axis must be 0, 1 or 2");
     if (s->stepped) return fail(KW_ESTATE, "plans are fixed after the first step");
     LaunchCfg save = s->cfg;
+    const bool save_off = s->ys_off, save_zs_off = s->zs_off;
+    if (!hint) (axis < 2 ? s->ys_off : s->zs_off) = true;
     const int n = axis == 0 ? s->g.M : axis == 1 ? s->g.ny : s->g.nz;
     if (radices && n_radices > 0) {
         std::vector<int> rad(radices, radices + n_radices);
         FftPlan f, r;
         int eng;
-        if (!axis_plan(n, axis, &rad, eng, f, r))
+        if (!axis_plan(n, axis, &rad, eng, f, r)) {
+            s->ys_off = save_off;
+            s->zs_off = save_zs_off;
             return fail(KW_EINVAL, "radices do not form a schedule for length %d", n);
+        }
         (axis == 0 ? s->cfg.px : axis == 1 ? s->cfg.py : s->cfg.pz) = f;
         (axis == 0 ? s->cfg.pxi : axis == 1 ? s->cfg.pyi : s->cfg.pzi) = r;
         (axis == 0 ? s->cfg.eng_x : axis == 1 ? s->cfg.eng_y : s->cfg.eng_z) = eng;
@@ -1610,10 +1708,20 @@ int kw_set_plan(kw_sim *s, int axis, const int32_t *radices, int32_t n_radices, 
     }
     if (rc != KW_OK) {
         s->cfg = save;
+        s->ys_off = save_off;
+        s->zs_off = save_zs_off;
         return rc;
     }
     drop_graph(s);
     return KW_OK;
+}
+
+int kw_set_plan(kw_sim *s, int axis, const int32_t *radices, int32_t n_radices, int32_t tile) {
+    return apply_plan(s, axis, radices, n_radices, tile, false);
+}
+
+int kw_suggest_plan(kw_sim *s, int axis, const int32_t *radices, int32_t n_radices, int32_t tile) {
+    return apply_plan(s, axis, radices, n_radices, tile, true);
 }
 
 // --- state snapshots ----------------------------------------------------------

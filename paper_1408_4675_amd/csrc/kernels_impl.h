@@ -56,6 +56,10 @@ __device__ __forceinline__ float2 ld2(const float *p, size_t i) {
 __device__ __forceinline__ void st2(float *p, size_t i, float2 v) {
     *reinterpret_cast<float2 *>(p + i) = v;
 }
+// A value that is the same in every lane, told so to the compiler (block indices
+// that went through a division sit in vector registers otherwise, and with them
+// every base address computed from them: 32 registers for 16 elements)
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 // Element at a 32-bit byte offset from p, p uniform over the wavefront (a
 // requirement: the first active lane's p is used for all).  p
 // is read into scalar registers (readfirstlane) and accessed as global memory,
@@ -122,8 +126,7 @@ __device__ __attribute__((noinline)) float kappa_large(float x2) {
 // x <= 1.7, which covers CFL numbers up to about 0.6 at the corner of the
 // wavenumber cube); larger arguments take kappa_large.  No sqrt and no range
 // reduction on the common path.
-__device__ __forceinline__ float kappa_of_x2(float x2) {
-    if (x2 > 2.89f) return kappa_large(x2);
+__device__ __forceinline__ float kappa_poly(float x2) {
     float p = 1.0f / 355687428096000.0f;            //  1/17!
     p = p * x2 - 1.0f / 1307674368000.0f;           // -1/15!
     p = p * x2 + 1.0f / 6227020800.0f;              //  1/13!
@@ -133,6 +136,10 @@ __device__ __forceinline__ float kappa_of_x2(float x2) {
     p = p * x2 + 1.0f / 120.0f;                     //  1/5!
     p = p * x2 - 1.0f / 6.0f;                       // -1/3!
     return p * x2 + 1.0f;
+}
+__device__ __forceinline__ float kappa_of_x2(float x2) {
+    if (x2 > kKappaPolyMax) return kappa_large(x2);
+    return kappa_poly(x2);
 }
 
 // ---------------------------------------------------------------------------
@@ -223,6 +230,23 @@ struct YArgs {
     double harm_wdt;
 };
 
+// The prologue, run by one block of the first kernel of a step (inlined: a
+// call to an out-of-line prologue costs the kernel a stack frame, scratch
+// memory and more registers for every block)
+__device__ __forceinline__ void y_prologue(const YArgs &a, bool mine) {
+    if (a.prologue && mine) {
+        const int n = *a.cnt.step;
+        __syncthreads();
+        if (threadIdx.x == 0) *a.cnt.step = n + 1;
+        for (int e = threadIdx.x; e < a.src.n_elements; e += blockDim.x) a.src.drive[e] = drive_at(a.src, e, n);
+        for (int h = threadIdx.x; h < a.n_harm; h += blockDim.x) {
+            const double th = a.harm_wdt * (double)(h + 1) * (double)(n + 1);
+            a.hw[2 * h] = (float)cos(th);
+            a.hw[2 * h + 1] = (float)sin(th);
+        }
+    }
+}
+
 // MAXT: 512, or 1024 for the wide column tiles of long axes (fixed engines
 // only, whose register count fits the 128 registers a 1024-thread block allows)
 template <class Eng, bool INV, int MAXT = 512>
@@ -235,7 +259,7 @@ __global__ void __launch_bounds__(MAXT) kw_ypass(YArgs a) {
     const int b = tid % a.tb, t = tid / a.tb;
     int blk, rep_;
     if (!xcd_order(blockIdx.x, line_group(a.tb), 1, a.ntiles * a.nz, blk, rep_)) return;
-    const int tile = blk % a.ntiles, iz = blk / a.ntiles;
+    const int iz = uniform(blk / a.ntiles), tile = uniform(blk - iz * a.ntiles);
     const int col = tile * a.tb + b;
     const bool ok = col < a.M;
     // element (row t + m step, column col) of this block's tile: uniform base
@@ -244,21 +268,7 @@ __global__ void __launch_bounds__(MAXT) kw_ypass(YArgs a) {
     const float2 *const base = pick3(a.f, (int)blockIdx.z) + tile_off;
     const uint32_t lane = (uint32_t)(t * a.M + b) * 8u;
 
-    if constexpr (!INV) {
-        // (a call to an out-of-line prologue costs the kernel a stack frame:
-        // scratch memory and more registers for every block)
-        if (a.prologue && blk == 0 && blockIdx.z == 0) {
-            const int n = *a.cnt.step;
-            __syncthreads();
-            if (tid == 0) *a.cnt.step = n + 1;
-            for (int e = tid; e < a.src.n_elements; e += blockDim.x) a.src.drive[e] = drive_at(a.src, e, n);
-            for (int h = tid; h < a.n_harm; h += blockDim.x) {
-                const double th = a.harm_wdt * (double)(h + 1) * (double)(n + 1);
-                a.hw[2 * h] = (float)cos(th);
-                a.hw[2 * h + 1] = (float)sin(th);
-            }
-        }
-    }
+    if constexpr (!INV) y_prologue(a, blk == 0 && blockIdx.z == 0);
 
     float2 v[E];
     const int ny = a.ny, h = (ny - 1) / 2;
@@ -543,8 +553,8 @@ __global__ void __launch_bounds__(MAXT) kw_zfused(ZArgs a) {
     c.t = t;
     c.b = b;
     c.M = M;
-    const int tile = blk % a.ntiles;
-    c.iy = blk / a.ntiles;
+    c.iy = uniform(blk / a.ntiles);
+    const int tile = uniform(blk - c.iy * a.ntiles);
     const int col = tile * a.tb + b;
     c.ok = col < M;
     c.stride = (size_t)M * ny;

@@ -1,5 +1,6 @@
 // Launchers of the y-pass and fused z-pass kernels (all FFT engines).
 #include "kernels_impl.h"
+#include "zstaged.h"
 
 namespace kw {
 
@@ -25,8 +26,8 @@ hipError_t launch_ypass(hipStream_t s, const GridDev &g, const LaunchCfg &c, con
         a.n_harm = sen->n_harm;
         a.harm_wdt = sen->harm_wdt;
     }
-    a.ntiles = (g.M + a.tb - 1) / a.tb;
     a.nz = g.nz;
+    a.ntiles = (g.M + a.tb - 1) / a.tb;
     // one workgroup per (tile, z plane) in XCD-aware order (xcd_order), per field
     dim3 grid(xcd_grid(a.ntiles * g.nz, line_group(a.tb), 1), 1, nfields);
     dim3 block(a.tb * a.plan.L);
@@ -91,6 +92,7 @@ hipError_t launch_zfused(hipStream_t s, const GridDev &g, const LaunchCfg &c, co
         a.add0[0] = add0[0];
         a.add0[1] = add0[1];
     }
+    if (c.zs && !(c.zs_skip >> mode & 1)) return launch_zstaged(s, c, mode, a, z_outputs(mode));
     int eng = c.eng_z;
     if (mode == ZM_ABSM) {
         // the merged absorption's own engine and plans (see LaunchCfg)

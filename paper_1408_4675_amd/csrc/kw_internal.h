@@ -32,6 +32,9 @@ __host__ __device__ inline int plan_radix(const FftPlan &P, int p) {
     return (int)((P.code >> (6 * p)) & 63ull);
 }
 
+// largest x^2 = (c_ref dt k / 2)^2 for which kappa is evaluated as a polynomial
+constexpr float kKappaPolyMax = 2.89f;
+
 // One real field or spectrum array plus an optional per-point map: when
 // `map` is null the scalar is used everywhere.
 struct Coef {
@@ -155,6 +158,22 @@ inline bool eng_fixed(int e) {
 // a second spectrum or sums per thread (they take the generic engines' paths)
 inline bool eng_wide(int e) { return e == ENG_F20 || e == ENG_F32; }
 
+// i / d for i, d < 2^16 by a multiplication
+struct FastDiv {
+    uint32_t d, m;
+    FastDiv() = default;
+    __host__ explicit FastDiv(int n) : d((uint32_t)n), m(n > 1 ? (uint32_t)(((1ull << 32) + n - 1) / n) : 0) {}
+    __device__ __forceinline__ int div(int i) const {
+        return d == 1 ? i : (int)(((unsigned long long)(uint32_t)i * m) >> 32);
+    }
+};
+
+// One axis of the staged transforms (staged.h): radices of its in-place stages and w[p] = r[0] .. r[p-1], the distance of a stage's elements
+struct StageAxis {
+    int n, np;
+    int r[3], w[3];
+    FastDiv dw1, d1, d2;     // by w[1], r[1], r[2] (three-stage axes)
+};
 struct LaunchCfg {
     int eng_x, eng_y, eng_z; // EngId per axis
     FftPlan px, pxi;         // x forward plan (length M) and the plan of the inverse
@@ -167,6 +186,12 @@ struct LaunchCfg {
     int eng_za;              // the merged absorption z pass: engine, plans and
     FftPlan pza, pzai;       // columns per block (the z pass's own unless a
     int tb_za;               // better one is known for its length)
+    int zs;                  // z pass on staged transforms (kernels_zs.hip): 0 no, 1 the
+                             // kernels for powers of two, 2 those for any length
+    StageAxis zs_axis;
+    unsigned zs_skip;        // modes (bit ZM_*) that stay on the engines
+    int zs_tb, zs_tb_grad, zs_tb_absm, zs_grad3, zs_threads;  // columns a tile; the gradient's
+                             // outputs from one block; threads
 };
 
 // LDS of the three-group density kernel (generic engines): the FFT buffers

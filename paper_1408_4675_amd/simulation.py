@@ -221,7 +221,7 @@ class Simulation:
             from .autotune import lookup
             for axis, (rad, tile) in lookup(sc.grid).items():
                 try:
-                    self.set_plan(axis, rad, tile)
+                    self._plan(self.lib.kw_suggest_plan, axis, rad, tile)
                     self.plans[axis] = (rad, tile)
                 except A.KwError:
                     pass
@@ -294,8 +294,11 @@ class Simulation:
         A.check(self.lib.kw_profile(self.handle, 1 if on else 0))
 
     def set_plan(self, axis: int, radices, tile: int = 0):
+        self._plan(self.lib.kw_set_plan, axis, radices, tile)
+
+    def _plan(self, call, axis: int, radices, tile: int):
         arr = (C.c_int32 * len(radices))(*radices) if radices else None
-        A.check(self.lib.kw_set_plan(self.handle, axis, arr, len(radices) if radices else 0, tile))
+        A.check(call(self.handle, axis, arr, len(radices) if radices else 0, tile))
 
     def stats(self) -> dict:
         st = A.KwStats()
