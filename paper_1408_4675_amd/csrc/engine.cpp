@@ -346,6 +346,23 @@ void pick_zstaged(const GridDev &g, double kx_max, double ky_max, double kz_max,
     c.zs = pow2 ? 1 : 2;
 }
 
+// Whether the y pass runs on staged transforms, and its tiles: the lengths of
+// the generic engine (the fixed-width engines' single-purpose kernels measured
+// equal or faster on theirs)
+void pick_ystaged(const GridDev &g, size_t max_lds, LaunchCfg &c) {
+    const int n = g.ny;
+    c.ys = 0;
+    if (eng_fixed(c.eng_y) || !stage_axis(n, false, c.ys_axis)) return;
+    auto lds = [&](int tb) { return 8 * ((size_t)n + (size_t)n * tb); };
+    int tb = 16;
+    while (tb > 1 && lds(tb) > 80 * 1024) tb /= 2;
+    while (tb > 8 && ((g.M + tb - 1) / tb) * g.nz < 512) tb /= 2;
+    if (lds(tb) > max_lds) return;
+    c.ys_tb = tb;
+    c.ys_threads = std::min(512, std::max(64, (n * tb / stage_rmax(c.ys_axis) + 63) / 64 * 64));
+    c.ys = 2;
+}
+
 // ---------------------------------------------------------------------------
 // workspace layout
 // ---------------------------------------------------------------------------
@@ -925,6 +942,8 @@ int pick_tiles(kw_sim *s, int tile_y, int tile_z) {
     }
     pick_zstaged(g, kPi / s->grid.dx, kPi / s->grid.dy, kPi / s->grid.dz, s->max_lds, c);
     if (s->zs_off) c.zs = 0;
+    pick_ystaged(g, s->max_lds, c);
+    if (s->ys_off) c.ys = 0;
     // the column passes address an element of their tile by a 32-bit byte offset
     const uint64_t zlane = ((uint64_t)std::max(c.pz.L, c.pza.L) * g.M * g.ny + std::max(c.tb_z, c.tb_za)) * 8;
     if (zlane >= (1ull << 32))

@@ -1,5 +1,6 @@
 // Launchers of the y-pass and fused z-pass kernels (all FFT engines).
 #include "kernels_impl.h"
+#include "ystaged.h"
 #include "zstaged.h"
 
 namespace kw {
@@ -27,6 +28,7 @@ hipError_t launch_ypass(hipStream_t s, const GridDev &g, const LaunchCfg &c, con
         a.harm_wdt = sen->harm_wdt;
     }
     a.nz = g.nz;
+    if (c.ys) return launch_ystaged(s, c, a, inverse, nfields);
     a.ntiles = (g.M + a.tb - 1) / a.tb;
     // one workgroup per (tile, z plane) in XCD-aware order (xcd_order), per field
     dim3 grid(xcd_grid(a.ntiles * g.nz, line_group(a.tb), 1), 1, nfields);

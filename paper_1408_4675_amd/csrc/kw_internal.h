@@ -192,6 +192,8 @@ struct LaunchCfg {
     unsigned zs_skip;        // modes (bit ZM_*) that stay on the engines
     int zs_tb, zs_tb_grad, zs_tb_absm, zs_grad3, zs_threads;  // columns a tile; the gradient's
                              // outputs from one block; threads
+    int ys, ys_tb, ys_threads;   // y pass on staged transforms (kernels_ys.hip), as zs
+    StageAxis ys_axis;
 };
 
 // LDS of the three-group density kernel (generic engines): the FFT buffers

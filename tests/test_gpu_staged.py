@@ -62,6 +62,12 @@ def test_z_columns(kw, n, medium):
     _check(kw, _case(8 if n > 64 else 40, 6, n, medium))
 
 
+@pytest.mark.parametrize("n", COLUMNS)
+def test_y_columns(kw, n):
+    """The y pass, its packed column 0 included (kx = 0 and Nyquist)."""
+    _check(kw, _case(8 if n > 64 else 36, n, 5, "maps"))
+
+
 def test_kappa_beyond_the_polynomial(kw):
     """Time steps whose kappa argument leaves the polynomial's range keep the
     pass that evaluates the sine."""
