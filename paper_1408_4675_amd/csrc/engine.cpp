@@ -260,15 +260,25 @@ bool axis_plan(int n, int axis, const std::vector<int> *rad, int &eng, FftPlan &
     return true;
 }
 
-// Stages of a column of the staged transforms (staged.h): the fewest stages, then
-// the smallest largest radix, of radices the kernels are built for (kPow2Y,
-// kAnyY).  At least two, one at each end of the column; the first has radix 1
-// where the length is a radix itself.
-bool stage_axis(int n, bool pow2, StageAxis &A) {
+// Stages of an axis of the staged transforms (staged.h): the fewest stages, then
+// the smallest largest radix, of radices the kernels are built for (kPow2Y, kAnyY;
+// kPow2M .. kAnyP for x rows).  At least two -- one at each end of a column; the
+// update's and the real-transform split's of a row -- where the first has radix 1
+// if the length is a radix itself; the columns of a plane may have one.
+enum { ST_COLUMN, ST_ROW, ST_PLANE };
+bool stage_axis(int n, int kind, bool pow2, StageAxis &A) {
+    // (of equals the largest last radix: an x row's update runs over M / r[0]
+    // neighbouring points)
     std::vector<int> last = {16, 8, 4, 2};
     if (!pow2) last = {16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2};
     std::vector<int> first = last;
-    first.push_back(1);
+    if (kind == ST_ROW) {
+        last = {8, 4, 2};
+        first = {8, 4, 2};
+        if (!pow2) last = {12, 10, 9, 8, 6, 5, 4, 3, 2};
+        if (!pow2) first = {8, 6, 5, 4, 3, 2};
+    }
+    if (kind != ST_PLANE) first.push_back(1);
     int best[3] = {0, 0, 0}, best_np = 4, best_max = INT_MAX;
     auto take = [&](int np, int a, int b, int c) {
         const int mx = std::max(a, std::max(b, c));
@@ -282,6 +292,7 @@ bool stage_axis(int n, bool pow2, StageAxis &A) {
     for (int c : last) {
         if (n % c) continue;
         const int m = n / c;
+        if (m == 1 && kind == ST_PLANE) take(1, c, 0, 0);
         for (int a : first) {
             if (m == a) take(2, a, c, 0);
             if (a == 1 || m % a) continue;
@@ -299,6 +310,8 @@ bool stage_axis(int n, bool pow2, StageAxis &A) {
         A.w[p] = w;
         w *= A.r[p];
     }
+    A.rl = A.r[best_np - 1];
+    A.wl = A.w[best_np - 1];
     A.dw1 = FastDiv(A.w[1]);
     A.d1 = FastDiv(A.r[1]);
     A.d2 = FastDiv(A.r[2]);
@@ -313,7 +326,7 @@ void pick_zstaged(const GridDev &g, double kx_max, double ky_max, double kz_max,
     const int n = g.nz;
     c.zs = 0;
     const bool pow2 = is_pow2(n);
-    if (!stage_axis(n, pow2, c.zs_axis)) return;
+    if (!stage_axis(n, ST_COLUMN, pow2, c.zs_axis)) return;
     // The fixed-width engines keep the gradient and the merged absorption of 256
     // and 1024 points, lengths that their 16- and 32-wide threads transform in
     // two passes (gradient at 1024: three, in 4-column tiles).  Staged against
@@ -352,7 +365,7 @@ void pick_zstaged(const GridDev &g, double kx_max, double ky_max, double kz_max,
 void pick_ystaged(const GridDev &g, size_t max_lds, LaunchCfg &c) {
     const int n = g.ny;
     c.ys = 0;
-    if (eng_fixed(c.eng_y) || !stage_axis(n, false, c.ys_axis)) return;
+    if (eng_fixed(c.eng_y) || !stage_axis(n, ST_COLUMN, false, c.ys_axis)) return;
     auto lds = [&](int tb) { return 8 * ((size_t)n + (size_t)n * tb); };
     int tb = 16;
     while (tb > 1 && lds(tb) > 80 * 1024) tb /= 2;
@@ -361,6 +374,79 @@ void pick_ystaged(const GridDev &g, size_t max_lds, LaunchCfg &c) {
     c.ys_tb = tb;
     c.ys_threads = std::min(512, std::max(64, (n * tb / stage_rmax(c.ys_axis) + 63) / 64 * 64));
     c.ys = 2;
+}
+
+// Which x passes of a step run on staged transforms, which of them on z planes, and
+// their blocks
+void pick_xstaged(const GridDev &g, bool absorbing, bool merged, size_t max_lds, LaunchCfg &c) {
+    c.xs = 0;
+    c.xs_passes = c.planes = 0;
+    const bool row_pow2 = is_pow2(g.M), pow2 = row_pow2 && is_pow2(g.ny);
+    auto layout = [&](bool p2) {
+        if (!stage_axis(g.M, ST_ROW, p2, c.xs_axis)) return false;
+        // rows an odd number of slots apart (lanes along the rows meet every bank)
+        c.xs_pad = c.xs_axis.r[0] % 2 == 0 ? 1 : 0;
+        c.xs_pitch = (g.M + c.xs_pad * (g.M / c.xs_axis.r[0])) | 1;
+        return true;
+    };
+    const int sets[3] = {1, 3, merged ? 1 : 2};
+    const int passes = absorbing ? 3 : 2;
+    // Planes: the velocity pass, three blocks a plane, wherever a plane fits LDS and
+    // the blocks fill half the chip or the planes are small; the other two, one block a
+    // plane, on planes so small that launches and latency are all there is.  us, planes :
+    // y pass, x pass, y pass: velocity 64^3 17 : 21, 96^3 28 : 41, 128^3 37 : 51, 160^3
+    // 83 : 127 (rows 113), 250 x 135 x 90 92 : 122; density 48 x 20 x 18 30 : 35, but
+    // 64^3 36 : 30, 96^3 55 : 46; pressure 48 x 20 x 18 18 : 21, 64^3 23 : 19, 96^3 35 : 33
+    unsigned planes = g.M * g.ny <= 1536 ? 7u : 3 * g.nz >= 144 || g.M * g.ny <= 4096 ? 1u << XS_VEL : 0u;
+    // Rows: the lengths of the generic engine, whose passes of a smaller radix than its
+    // largest leave threads idle: us, rows : engine, velocity / density / pressure
+    // 250 x 135 x 90 (125 = 5 25) 53 : 150 / 68 : 249 / 45 : 148; 160^3 63 : 76 / 90 : 91 /
+    // 57 : 60; 360 x 270 x 120 175 : 189 / 264 : 289 / 168 : 164; 450 x 480 x 324 989 : 1061 /
+    // 1512 : 1686 / 522 : 540.  The 8- and 12-wide engines keep theirs (256^3 density
+    // 388 : 193, 192^3 158 : 145, 96^3 32 : 28)
+    const unsigned rows = eng_fixed(c.eng_x) ? 0u : 7u;
+    bool set = pow2;
+    if (planes && layout(pow2) && stage_axis(g.ny, ST_PLANE, pow2, c.planes_y)) {
+        for (int p = 0; p < passes; ++p) {
+            if (!(planes >> p & 1) || xs_lds_bytes(g.M, g.ny, g.ny, sets[p], c.xs_pitch) > max_lds) continue;
+            c.planes |= 1u << p;
+            const int el = g.M * g.ny * sets[p];
+            c.planes_threads[p] = el > 10000 && p != XS_DEN ? 1024 : el > 2048 ? 512 : 256;
+        }
+    }
+    if (!c.planes) {
+        set = row_pow2;
+        if (!layout(set)) return;
+    }
+    c.xs_passes = c.planes;
+    for (int p = 0; p < passes; ++p) {
+        if (!(rows >> p & 1) || (c.planes >> p & 1)) continue;
+        // Rows of a set in a block: a block of 256 threads takes about as long as its
+        // values plus a thousand (its phases' latencies, its tables), and a CU holds
+        // four (density: three, by registers) with up to its share of LDS: the rows
+        // that make whole rounds of blocks cost least.  (250 x 135 x 90 pressure: 12 rows,
+        // 1013 blocks 45 us; 11 rows, 1105 blocks 65 us)
+        constexpr long kCUs = 256;
+        const int per_cu = p == XS_DEN ? 3 : 4;
+        long best = LONG_MAX;
+        int n = 0;
+        for (int r = 1; r <= g.rows; ++r) {
+            const long el = (long)r * g.M * sets[p];
+            const size_t lds = xs_lds_bytes(g.M, 0, r, sets[p], c.xs_pitch);
+            if (r > 1 && (el > 6144 || lds > max_lds / per_cu)) break;
+            if (lds > max_lds) break;
+            const long blocks = (long)((g.rows + r - 1) / r) * (p == XS_VEL ? 3 : 1);
+            const long cost = (blocks + kCUs * per_cu - 1) / (kCUs * per_cu) * (el + 1000);
+            if (cost < best) {
+                best = cost;
+                n = r;
+            }
+        }
+        if (n == 0) continue;
+        c.xs_rows[p] = n;
+        c.xs_passes |= 1u << p;
+    }
+    if (c.xs_passes) c.xs = set ? 1 : 2;
 }
 
 // ---------------------------------------------------------------------------
@@ -637,7 +723,7 @@ struct kw_sim {
     std::vector<Rec> recs;
     std::vector<hipEvent_t> pool;
     size_t max_lds = 64 * 1024;        // LDS bytes a block may use on this device
-    bool ys_off = false;            // the caller chose x or y schedules (kw_set_plan)
+    bool xy_off = false;            // the caller chose x or y schedules (kw_set_plan)
     bool zs_off = false;               // and the z schedule
     bool merged_abs = false;           // absorption terms merged (scalar c0^2 tau, c0^2 eta)
     bool rho0_sum_in_z = false;        // absorbing with a constant rho0: the divergence
@@ -743,14 +829,17 @@ hipError_t enqueue_step(kw_sim *s) {
     float2 *s123[3] = {S[1], S[2], S[3]};
     float2 *s456[3] = {S[4], S[5], S[6]};
     float *const *rec = s->rec[0] ? s->rec : nullptr;
-    // with fused plane passes the launches of the y passes around an x pass
-    // drop out (the x pass's launcher runs them), and with them their traffic
+    // the y passes around an x pass that runs on planes are part of it
+#define KW_Y(pass, cls, units, call)                                            \
+    do {                                                                        \
+        if (!(c.planes >> (pass) & 1)) KW_L(cls, units, call);                  \
+    } while (0)
     KW_L(KC_YFWD, 2, launch_ypass(st, g, c, t, s0, 1, false, &s->counters, &s->src, &s->sen));
     KW_L(KC_ZGRAD, 4, launch_zfused(st, g, c, t, ZM_GRAD, s0, s123));
-    KW_L(KC_YINV, 6, launch_ypass(st, g, c, t, s123, 3, true, nullptr, nullptr));
+    KW_Y(XS_VEL, KC_YINV, 6, launch_ypass(st, g, c, t, s123, 3, true, nullptr, nullptr));
     KW_L(KC_XVEL, 12 + (ms.het[MED_DTRX] ? 3 : 0),
          launch_xvel(st, g, c, t, s->med, s123, s->buf.u, s->src, s->sen, s->counters));
-    KW_L(KC_YFWD, 6, launch_ypass(st, g, c, t, s123, 3, false, nullptr, nullptr));
+    KW_Y(XS_VEL, KC_YFWD, 6, launch_ypass(st, g, c, t, s123, 3, false, nullptr, nullptr));
     if (s->rho0_sum_in_z) {
         // Constant rho0: the tau term of Eq. (8) transforms rho0 sum du, whose
         // (kx, ky) spectrum is rho0 nx ny times the sum of the three
@@ -761,27 +850,28 @@ hipError_t enqueue_step(kw_sim *s) {
         // forward x and y transform less, and no write of a spectrum.
         const float r0nxny = (float)((double)s->med.rho0.scalar * g.nx * g.ny);
         KW_L(KC_ZDIV, 6, launch_zfused(st, g, c, t, ZM_DIV, s123, s456));
-        KW_L(KC_YINV, 6, launch_ypass(st, g, c, t, s456, 3, true, nullptr, nullptr, nullptr, s123));
-        float2 *rho_out[2] = {S[0], S[0]};
-        KW_L(KC_XDEN, 11, launch_xden(st, g, c, t, s->med, s->src, s->sen, s->counters, s123,
+        KW_Y(XS_DEN, KC_YINV, 6, launch_ypass(st, g, c, t, s456, 3, true, nullptr, nullptr, nullptr, s123));
+        float2 *rho_out[3] = {S[0], S[0], nullptr};
+        KW_L(KC_XDEN, 11, launch_xden(st, g, c, t, s->med, s->src, s->sen, s->counters,
+                                      c.planes >> XS_DEN & 1 ? s456 : s123,
                                       s->buf.rho, s->buf.rho_total, rho_out, true, rec));
-        KW_L(KC_YFWD, 2, launch_ypass(st, g, c, t, s0, 1, false, nullptr, nullptr));
+        KW_Y(XS_DEN, KC_YFWD, 2, launch_ypass(st, g, c, t, s0, 1, false, nullptr, nullptr));
         float2 *in[2] = {S[4], S[0]};
         float2 *add0[2] = {S[5], S[6]};
         const double med_units = (ms.het[MED_C0SQ] ? 1 : 0) + (ms.het[MED_NL] ? 1 : 0) +
                                  (ms.het[MED_TA] ? 2 : 0);
         if (s->merged_abs) {
-            float2 *s1[1] = {S[1]};
+            float2 *s1[3] = {S[1], nullptr, S[3]};
             KW_L(KC_ZABS, 5, launch_zfused(st, g, c, t, ZM_ABSM, in, s1, s->med.ta.scalar * r0nxny,
                                            s->med.tb.scalar, add0));
-            KW_L(KC_YINV, 2, launch_ypass(st, g, c, t, s1, 1, true, nullptr, nullptr));
+            KW_Y(XS_EOS, KC_YINV, 2, launch_ypass(st, g, c, t, s1, 1, true, nullptr, nullptr));
             KW_L(KC_XEOS, 3 + med_units + sens_units,
                  launch_xeos(st, g, c, t, s->med, s->src, s->sen, s->counters, s1,
                              s->buf.rho_total, S[0], true));
         } else {
-            float2 *s12[2] = {S[1], S[2]};
+            float2 *s12[3] = {S[1], S[2], S[3]};
             KW_L(KC_ZABS, 6, launch_zfused(st, g, c, t, ZM_ABS, in, s12, r0nxny, 1.0f, add0));
-            KW_L(KC_YINV, 4, launch_ypass(st, g, c, t, s12, 2, true, nullptr, nullptr));
+            KW_Y(XS_EOS, KC_YINV, 4, launch_ypass(st, g, c, t, s12, 2, true, nullptr, nullptr));
             KW_L(KC_XEOS, 4 + med_units + sens_units,
                  launch_xeos(st, g, c, t, s->med, s->src, s->sen, s->counters, s12,
                              s->buf.rho_total, S[0]));
@@ -790,40 +880,41 @@ hipError_t enqueue_step(kw_sim *s) {
         return hipSuccess;
     }
     KW_L(KC_ZDIV, 6, launch_zfused(st, g, c, t, ZM_DIV, s123, s456));
-    KW_L(KC_YINV, 6, launch_ypass(st, g, c, t, s456, 3, true, nullptr, nullptr));
+    KW_Y(XS_DEN, KC_YINV, 6, launch_ypass(st, g, c, t, s456, 3, true, nullptr, nullptr));
     if (absorbing) {
-        float2 *out2[2] = {S[1], S[2]};
+        float2 *out2[3] = {S[1], S[2], S[3]};
         KW_L(KC_XDEN, 12 + (ms.het[MED_RHO0] ? 1 : 0),
              launch_xden(st, g, c, t, s->med, s->src, s->sen, s->counters, s456, s->buf.rho,
                          s->buf.rho_total, out2, false, rec));
         float2 *s12[2] = {S[1], S[2]};
-        float2 *s45[2] = {S[4], S[5]};
-        KW_L(KC_YFWD, 4, launch_ypass(st, g, c, t, s12, 2, false, nullptr, nullptr));
+        float2 *s45[3] = {S[4], S[5], S[6]};
+        KW_Y(XS_DEN, KC_YFWD, 4, launch_ypass(st, g, c, t, s12, 2, false, nullptr, nullptr));
         const double med_units = (ms.het[MED_C0SQ] ? 1 : 0) + (ms.het[MED_NL] ? 1 : 0) +
                                  (ms.het[MED_TA] ? 2 : 0);
         if (s->merged_abs) {
             // scalar c0^2 tau and c0^2 eta: both terms of Eq. (8) in one spectrum
             KW_L(KC_ZABS, 3, launch_zfused(st, g, c, t, ZM_ABSM, s12, s45, s->med.ta.scalar,
                                            s->med.tb.scalar));
-            KW_L(KC_YINV, 2, launch_ypass(st, g, c, t, s45, 1, true, nullptr, nullptr));
+            KW_Y(XS_EOS, KC_YINV, 2, launch_ypass(st, g, c, t, s45, 1, true, nullptr, nullptr));
             KW_L(KC_XEOS, 3 + med_units + sens_units,
                  launch_xeos(st, g, c, t, s->med, s->src, s->sen, s->counters, s45,
                              s->buf.rho_total, S[0], true));
         } else {
             KW_L(KC_ZABS, 4, launch_zfused(st, g, c, t, ZM_ABS, s12, s45));
-            KW_L(KC_YINV, 4, launch_ypass(st, g, c, t, s45, 2, true, nullptr, nullptr));
+            KW_Y(XS_EOS, KC_YINV, 4, launch_ypass(st, g, c, t, s45, 2, true, nullptr, nullptr));
             KW_L(KC_XEOS, 4 + med_units + sens_units,
                  launch_xeos(st, g, c, t, s->med, s->src, s->sen, s->counters, s45,
                              s->buf.rho_total, S[0]));
         }
     } else {
-        float2 *out1[2] = {S[0], nullptr};
+        float2 *out1[3] = {S[0], nullptr, S[1]};
         const double med_units = (ms.het[MED_RHO0] ? 1 : 0) + (ms.het[MED_C0SQ] ? 1 : 0) +
                                  (ms.het[MED_NL] ? 1 : 0);
         KW_L(KC_XDEN, 10 + med_units + sens_units,
              launch_xden(st, g, c, t, s->med, s->src, s->sen, s->counters, s456, s->buf.rho,
                          nullptr, out1, false, rec));
     }
+#undef KW_Y
 #undef KW_L
     s->kernels_per_step = nk;
     return hipSuccess;
@@ -943,7 +1034,8 @@ int pick_tiles(kw_sim *s, int tile_y, int tile_z) {
     pick_zstaged(g, kPi / s->grid.dx, kPi / s->grid.dy, kPi / s->grid.dz, s->max_lds, c);
     if (s->zs_off) c.zs = 0;
     pick_ystaged(g, s->max_lds, c);
-    if (s->ys_off) c.ys = 0;
+    pick_xstaged(g, s->med.absorbing, s->merged_abs, s->max_lds, c);
+    if (s->xy_off) c.ys = c.xs_passes = c.planes = 0;
     // the column passes address an element of their tile by a 32-bit byte offset
     const uint64_t zlane = ((uint64_t)std::max(c.pz.L, c.pza.L) * g.M * g.ny + std::max(c.tb_z, c.tb_za)) * 8;
     if (zlane >= (1ull << 32))
@@ -1704,15 +1796,15 @@ static int apply_plan(kw_sim *s, int axis, const int32_t *radices, int32_t n_rad
     if (axis < 0 || axis > 2) return fail(KW_EINVAL, "axis must be 0, 1 or 2");
     if (s->stepped) return fail(KW_ESTATE, "plans are fixed after the first step");
     LaunchCfg save = s->cfg;
-    const bool save_off = s->ys_off, save_zs_off = s->zs_off;
-    if (!hint) (axis < 2 ? s->ys_off : s->zs_off) = true;
+    const bool save_off = s->xy_off, save_zs_off = s->zs_off;
+    if (!hint) (axis < 2 ? s->xy_off : s->zs_off) = true;
     const int n = axis == 0 ? s->g.M : axis == 1 ? s->g.ny : s->g.nz;
     if (radices && n_radices > 0) {
         std::vector<int> rad(radices, radices + n_radices);
         FftPlan f, r;
         int eng;
         if (!axis_plan(n, axis, &rad, eng, f, r)) {
-            s->ys_off = save_off;
+            s->xy_off = save_off;
             s->zs_off = save_zs_off;
             return fail(KW_EINVAL, "radices do not form a schedule for length %d", n);
         }
@@ -1727,7 +1819,7 @@ static int apply_plan(kw_sim *s, int axis, const int32_t *radices, int32_t n_rad
     }
     if (rc != KW_OK) {
         s->cfg = save;
-        s->ys_off = save_off;
+        s->xy_off = save_off;
         s->zs_off = save_zs_off;
         return rc;
     }

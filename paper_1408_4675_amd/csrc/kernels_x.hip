@@ -1,5 +1,6 @@
 // Launchers of the x-pass kernels (all FFT engines).
 #include "kernels_impl.h"
+#include "xstaged.h"
 
 namespace kw {
 
@@ -37,10 +38,11 @@ hipError_t launch_xvel(hipStream_t s, const GridDev &g, const LaunchCfg &c, cons
         a.Sout[i] = S[i];
         a.fld[i] = u[i];
     }
-    dim3 grid((g.rows + c.tb_x - 1) / c.tb_x, 3);
-    dim3 block(c.tb_x * c.px.L);
     const int fl = (sen.u_series ? XV_USER : 0) |
                    (src.row_ptr && src.kind == KW_SOURCE_FORCE ? XV_FORCE : 0);
+    if (c.xs_passes >> XS_VEL & 1) return launch_xs_vel(s, c, a, fl != 0);
+    dim3 grid((g.rows + c.tb_x - 1) / c.tb_x, 3);
+    dim3 block(c.tb_x * c.px.L);
     const size_t lds = x_lds(g, c, fl != 0);
     switch (fl) {
     case 0: KW_ENGINE_SWITCH(c.eng_x, hipLaunchKernelGGL((kw_xvel<Eng, 0>), grid, block, lds, s, a)); break;
@@ -75,6 +77,7 @@ hipError_t launch_xden(hipStream_t s, const GridDev &g, const LaunchCfg &c, cons
     a.Sout[0] = Sout[0];
     a.Sout[1] = Sout[1];
     a.rho_total = rho_total;
+    if (c.xs_passes >> XS_DEN & 1) return launch_xs_den(s, c, a, reinterpret_cast<float *>(Sout[2]));
     if (!eng_fixed(c.eng_x) || eng_general(c.eng_x) == ENG_F12 || eng_wide(c.eng_x)) {
         // generic and mixed-radix engines: three thread groups per row (see
         // kw_xden3; their wider register arrays leave no room for the sums)
@@ -132,13 +135,15 @@ hipError_t launch_xeos(hipStream_t s, const GridDev &g, const LaunchCfg &c, cons
     a.sen = sen;
     a.cnt = cnt;
     a.Sin[0] = Sin[0];
-    a.Sin[1] = Sin[1];
+    if (!merged) a.Sin[1] = Sin[1];
     a.rho_total = const_cast<float *>(rho_total);
     a.Sout[0] = Sout;
     // mask sensor points and pressure-source values are picked out of a row
     // through a line that aliases the row's FFT buffer (no LDS of its own)
     const bool mask = sen.row_ptr != nullptr && !sen.all_points;
     const bool psrc = src.row_ptr != nullptr && src.kind == KW_SOURCE_PRESSURE;
+    if (c.xs_passes >> XS_EOS & 1)
+        return launch_xs_eos(s, c, a, reinterpret_cast<float *>(Sin[2]), mask || psrc, merged);
     const bool extra = sen.p_min != nullptr || sen.harm != nullptr || psrc;
     dim3 grid((g.rows + c.tb_x - 1) / c.tb_x);
     dim3 block(c.tb_x * c.px.L);

@@ -167,9 +167,9 @@ __global__ void __launch_bounds__(512) kw_zstaged(ZSArgs a) {
         __syncthreads();
     }
     // last forward stage, operator, last inverse stage
-    const int w = p.ax.w[p.ax.np - 1];
+    const int w = p.ax.wl;
     const float s0 = (MODE == ZM_ABSM || (MODE == ZM_ABS && o == 0)) ? z.sa : 1.0f;
-    with_radix<RS>(p.ax.r[p.ax.np - 1], [&](auto RC) __attribute__((always_inline)) {
+    with_radix<RS>(p.ax.rl, [&](auto RC) __attribute__((always_inline)) {
         constexpr int R = decltype(RC)::value;
         const int nt = w << T.ltb, step = w << T.ltb;
         for (int i = threadIdx.x; i < nt; i += blockDim.x) {
@@ -260,7 +260,7 @@ __global__ void __launch_bounds__(512) kw_zstaged(ZSArgs a) {
     });
     if (pairing) {                                           // block-uniform
         zs_pairs<MODE, NOUT>(z, T, sh2, dzl, iy, o, s0);
-        with_radix<RS>(p.ax.r[p.ax.np - 1], [&](auto RC) __attribute__((always_inline)) {
+        with_radix<RS>(p.ax.rl, [&](auto RC) __attribute__((always_inline)) {
             constexpr int R = decltype(RC)::value;
             const int step = w << T.ltb;
             for (int b = threadIdx.x; b < w * NOUT; b += blockDim.x) {

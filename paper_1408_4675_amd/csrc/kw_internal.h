@@ -172,8 +172,21 @@ struct FastDiv {
 struct StageAxis {
     int n, np;
     int r[3], w[3];
+    int rl, wl;              // r and w of the last stage
     FastDiv dw1, d1, d2;     // by w[1], r[1], r[2] (three-stage axes)
 };
+// LDS of a staged x pass: tables (two of M, one of nyt values -- ny where the y
+// transforms are part of it -- and three words a row) and its sets of rows, `pitch`
+// values apart
+__host__ __device__ inline int xs_table_slots(int M, int nyt, int rows) {
+    return 2 * M + nyt + (3 * rows + 1) / 2;
+}
+inline size_t xs_lds_bytes(int M, int nyt, int rows, int sets, int pitch) {
+    return 8 * ((size_t)xs_table_slots(M, nyt, rows) + (size_t)sets * rows * pitch);
+}
+
+enum { XS_VEL = 0, XS_DEN = 1, XS_EOS = 2 };   // the x passes of a step
+
 struct LaunchCfg {
     int eng_x, eng_y, eng_z; // EngId per axis
     FftPlan px, pxi;         // x forward plan (length M) and the plan of the inverse
@@ -186,6 +199,13 @@ struct LaunchCfg {
     int eng_za;              // the merged absorption z pass: engine, plans and
     FftPlan pza, pzai;       // columns per block (the z pass's own unless a
     int tb_za;               // better one is known for its length)
+    // x passes on staged transforms (xstaged_impl.h): 0 no, 1 kernels for powers of
+    // two, 2 for any length; which of them (bits XS_*) run so, which on z planes with the
+    // y transforms included; rows of a set in a block, LDS row layout (see pcol)
+    int xs;
+    unsigned xs_passes, planes;
+    int xs_rows[3], xs_pad, xs_pitch, planes_threads[3];
+    StageAxis xs_axis, planes_y;
     int zs;                  // z pass on staged transforms (kernels_zs.hip): 0 no, 1 the
                              // kernels for powers of two, 2 those for any length
     StageAxis zs_axis;

@@ -123,8 +123,8 @@ __device__ __forceinline__ void col_middle(const ColPlan &a, const ColTile &T, f
 template <RadixSet RS>
 __device__ __forceinline__ void col_load_last(const ColPlan &a, const ColTile &T, const float2 *src,
                                               int cols, float2 *sh, bool join0) {
-    const int w = a.ax.w[a.ax.np - 1];
-    with_radix<RS>(a.ax.r[a.ax.np - 1], [&](auto RC) __attribute__((always_inline)) {
+    const int w = a.ax.wl;
+    with_radix<RS>(a.ax.rl, [&](auto RC) __attribute__((always_inline)) {
         constexpr int R = decltype(RC)::value;
         const int nt = w << T.ltb, step = w << T.ltb;
         for (int i = threadIdx.x; i < nt; i += blockDim.x) {
@@ -164,8 +164,8 @@ __device__ __forceinline__ void col_load_last(const ColPlan &a, const ColTile &T
 template <RadixSet RS>
 __device__ __forceinline__ void col_store_last(const ColPlan &a, const ColTile &T, float2 *dst,
                                                int cols, float2 *sh, bool keep0) {
-    const int w = a.ax.w[a.ax.np - 1];
-    with_radix<RS>(a.ax.r[a.ax.np - 1], [&](auto RC) __attribute__((always_inline)) {
+    const int w = a.ax.wl;
+    with_radix<RS>(a.ax.rl, [&](auto RC) __attribute__((always_inline)) {
         constexpr int R = decltype(RC)::value;
         const int nt = w << T.ltb, step = w << T.ltb;
         for (int i = threadIdx.x; i < nt; i += blockDim.x) {

@@ -91,3 +91,82 @@ def test_reverse_step(kw, shape):
     e = np.linalg.norm(out["source_gradient"] - gr["dJds"]) / np.linalg.norm(gr["dJds"])
     print("[case] %s dJ/ds %.2e" % (scen.name, e), flush=True)
     assert e <= TOL
+
+
+def _smooth(n):
+    while True:
+        m = n
+        for p in (2, 3, 5):
+            while m % p == 0:
+                m //= p
+        if m == 1:
+            return n
+        n += 1
+
+
+# packed row lengths nx / 2: one stage (the update's of radix 1), two, three, every
+# radix of the last stage, odd ones (no partner of its own in the middle)
+ROWS = [2, 3, 4, 5, 8, 9, 12, 15, 16, 18, 24, 25, 32, 45, 60, 64, 75, 81, 90, 96, 100, 125, 128, 135, 200,
+        225, 243, 250, 405, 500]
+
+
+@pytest.mark.parametrize("m", ROWS)
+@pytest.mark.parametrize("medium", ["maps", "water", "lossless"])
+def test_x_rows_on_planes(kw, m, medium):
+    """x passes on z planes (the velocity's, on small planes all three), with mass
+    source points and every point recorded."""
+    _check(kw, _case(2 * m, 6 if m < 200 else 5, 5, medium))
+
+
+@pytest.mark.parametrize("m", [15, 25, 45, 75, 80, 90, 100, 125, 135, 200, 225, 250, 405, 500])
+@pytest.mark.parametrize("medium", ["maps", "water", "lossless"])
+@pytest.mark.parametrize("mask", [False, True])
+def test_x_rows(kw, m, medium, mask):
+    """x passes on rows (planes too large for few blocks): full and ragged blocks,
+    mass source points, every point recorded or a mask with its series."""
+    _check(kw, _case(2 * m, _smooth(4097 // m + 1), 4, medium, mask))
+
+
+@pytest.mark.parametrize("shape", [(64, 64, 48), (96, 96, 50), (50, 45, 50), (128, 128, 48)])
+def test_velocity_on_large_planes(kw, shape):
+    """Velocity planes of the usual sizes (blocks of 512 and 1024 threads)."""
+    _check(kw, _case(*shape, "maps"))
+
+
+@pytest.mark.parametrize("shape", [(30, 8, 6), (100, 90, 4)], ids=["planes", "rows"])
+@pytest.mark.parametrize("kind,axis", [(sc.SOURCE_FORCE, 0), (sc.SOURCE_FORCE, 2), (sc.SOURCE_PRESSURE, 0)])
+@pytest.mark.parametrize("medium", ["maps", "water", "lossless"])
+def test_sources_and_sensors_between_the_transforms(kw, shape, kind, axis, medium):
+    """Force and pressure sources, and mask sensors with velocity series, harmonics and
+    p_min: written and read between the inverse and the forward x transform."""
+    import dataclasses
+    scen = _case(*shape, medium, mask=True)
+    rec = (sc.REC_P_MAX | sc.REC_P_MIN | sc.REC_P_RMS | sc.REC_P_SERIES | sc.REC_U_SERIES |
+           sc.REC_HARMONICS | sc.REC_P_FINAL | sc.REC_U_FINAL)
+    sen = dataclasses.replace(scen.sensor, record=rec, series_capacity=STEPS, n_harmonics=2)
+    # (a force of 1e6 m/s^2 gives dt F of about 0.02 m/s)
+    src = dataclasses.replace(scen.source, kind=kind, axis=axis)
+    _check(kw, scen.replace(source=src, sensor=sen))
+
+
+@pytest.mark.parametrize("shape", [(30, 8, 6), (100, 90, 4), (64, 64, 48)])
+def test_forced_schedules_agree(kw, shape):
+    """The engines, forced with kw_set_plan, and the staged passes give the same fields to
+    rounding (TOL), and a tuned schedule given as a hint changes nothing there."""
+    A, Simulation = kw
+    scen = _case(*shape, "maps")
+    outs = []
+    for mode in ("staged", "hint", "engine"):
+        sim = Simulation(scen, tune=False)
+        if mode != "staged":
+            call = sim.lib.kw_suggest_plan if mode == "hint" else sim.lib.kw_set_plan
+            for axis, n in enumerate((shape[0] // 2, shape[1], shape[2])):
+                rad = [2, n // 2] if n % 2 == 0 and n // 2 <= 16 else None
+                if rad or mode == "engine":
+                    sim._plan(call, axis, rad, 0)
+        sim.step(STEPS)
+        outs.append(sim.gather(A.KW_REC_P_FINAL, device=False).astype(np.float64))
+        sim.close()
+    if shape == (30, 8, 6):
+        assert np.linalg.norm(outs[1] - outs[0]) <= TOL * np.linalg.norm(outs[0])
+    assert np.linalg.norm(outs[2] - outs[0]) <= TOL * np.linalg.norm(outs[0])
