@@ -318,7 +318,21 @@ bool stage_axis(int n, int kind, bool pow2, StageAxis &A) {
     return true;
 }
 
-int stage_rmax(const StageAxis &A) { return std::max(A.r[0], std::max(A.r[1], A.r[2])); }
+// Threads of a block of tb columns, by the values of a thread: in two stages the smaller
+// radix, so that the stage of more tasks goes in one sweep; in powers of two the larger
+// one (the other takes two whole sweeps, and the block's registers let more blocks onto a
+// CU); in three stages 16, as their small radices would ask for more threads than a CU
+// keeps in flight of several blocks.  us of gradient / divergence / absorption, smaller
+// radix and larger: 96^3 (8 12) 15 / 13 / 12, 18 / 15 / 14; 192^3 (12 16) 44 / 46 / 33,
+// 48 / 48 / 37; 128^3 (8 16) 18 / 21 / 15, 17 / 19 / 15; 243 (9 3 9) with 9 values 45 /
+// 57 / 38, with 16 values 41 / 51 / 40
+int stage_threads(const StageAxis &A, int tb) {
+    const int rmax = std::max(A.r[0], std::max(A.r[1], A.r[2]));
+    int values = rmax;
+    if (A.np >= 3) values = std::max(16, rmax);
+    else if (A.np == 2 && (A.n & (A.n - 1))) values = std::min(A.r[0], A.r[1]);
+    return std::min(512, std::max(64, (A.n * tb / values + 63) / 64 * 64));
+}
 
 // Whether the z pass runs on staged transforms, and its tiles
 void pick_zstaged(const GridDev &g, double kx_max, double ky_max, double kz_max, size_t max_lds,
@@ -354,8 +368,7 @@ void pick_zstaged(const GridDev &g, double kx_max, double ky_max, double kz_max,
     c.zs_grad3 = c.zs_tb_grad >= 8;
     if (!c.zs_grad3) c.zs_tb_grad = c.zs_tb;
     if (lds(c.zs_tb, 1) > max_lds || lds(c.zs_tb_absm, 2) > max_lds) return;
-    // about one task a thread in the stage of the largest radix
-    c.zs_threads = std::min(512, std::max(64, (n * c.zs_tb / stage_rmax(c.zs_axis) + 63) / 64 * 64));
+    c.zs_threads = stage_threads(c.zs_axis, c.zs_tb);
     c.zs = pow2 ? 1 : 2;
 }
 
@@ -372,7 +385,7 @@ void pick_ystaged(const GridDev &g, size_t max_lds, LaunchCfg &c) {
     while (tb > 8 && ((g.M + tb - 1) / tb) * g.nz < 512) tb /= 2;
     if (lds(tb) > max_lds) return;
     c.ys_tb = tb;
-    c.ys_threads = std::min(512, std::max(64, (n * tb / stage_rmax(c.ys_axis) + 63) / 64 * 64));
+    c.ys_threads = stage_threads(c.ys_axis, tb);
     c.ys = 2;
 }
 
