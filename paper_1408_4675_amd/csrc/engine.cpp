@@ -408,9 +408,10 @@ void pick_xstaged(const GridDev &g, bool absorbing, bool merged, size_t max_lds,
     // the blocks fill half the chip or the planes are small; the other two, one block a
     // plane, on planes so small that launches and latency are all there is.  us, planes :
     // y pass, x pass, y pass: velocity 64^3 17 : 21, 96^3 28 : 41, 128^3 37 : 51, 160^3
-    // 83 : 127 (rows 113), 250 x 135 x 90 92 : 122; density 48 x 20 x 18 30 : 35, but
-    // 64^3 36 : 30, 96^3 55 : 46; pressure 48 x 20 x 18 18 : 21, 64^3 23 : 19, 96^3 35 : 33
-    unsigned planes = g.M * g.ny <= 1536 ? 7u : 3 * g.nz >= 144 || g.M * g.ny <= 4096 ? 1u << XS_VEL : 0u;
+    // 83 : 127 (rows 113), 250 x 135 x 90 92 : 122; density and
+    // pressure with the y passes that they take in, 48 x 20 x 18 34 : 56, 64^3 47 : 57, but
+    // 96^3 87 : 82
+    unsigned planes = g.M * g.ny <= 2048 ? 7u : 3 * g.nz >= 144 || g.M * g.ny <= 4096 ? 1u << XS_VEL : 0u;
     // Rows: the lengths of the generic engine, whose passes of a smaller radix than its
     // largest leave threads idle: us, rows : engine, velocity / density / pressure
     // 250 x 135 x 90 (125 = 5 25) 53 : 150 / 68 : 249 / 45 : 148; 160^3 63 : 76 / 90 : 91 /
@@ -424,7 +425,7 @@ void pick_xstaged(const GridDev &g, bool absorbing, bool merged, size_t max_lds,
             if (!(planes >> p & 1) || xs_lds_bytes(g.M, g.ny, g.ny, sets[p], c.xs_pitch) > max_lds) continue;
             c.planes |= 1u << p;
             const int el = g.M * g.ny * sets[p];
-            c.planes_threads[p] = el > 10000 && p != XS_DEN ? 1024 : el > 2048 ? 512 : 256;
+            c.planes_threads[p] = p == XS_DEN ? 768 : el > 10000 ? 1024 : el > 2048 ? 512 : 256;
         }
     }
     if (!c.planes) {

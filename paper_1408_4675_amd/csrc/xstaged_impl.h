@@ -57,17 +57,41 @@ struct Rows {
     __device__ __forceinline__ float2 *set(int s) const { return sh + s * ny * pitch; }
 };
 
+// The threads at one set: number first of count
+struct Lanes {
+    int first, count;
+};
+// f(set, its threads) for NS sets (0: ns of them): on planes the sets side by side,
+// whole wavefronts each; on rows one after the other (there a set has a task for every
+// thread).  us on planes, one after the other and side by side: density 48 x 20 x 18
+// 30 -> 20, 64^3 36 -> 29, absorption terms 18 -> 14, 23 -> 18
+template <bool PLANES, int NS, class F>
+__device__ __forceinline__ void for_sets(int ns, F f) {
+    const int t = threadIdx.x, n = blockDim.x;
+    if constexpr (NS == 1) {
+#pragma unroll 1
+        for (int s = 0; s < 1; ++s) f(s, Lanes{t, n});     // (without the loop a variant spilled)
+    } else if constexpr (PLANES) {
+        const int per = n / warpSize / ns * warpSize;
+        const int s = uniform(t / per);
+        if (s < ns) f(s, Lanes{t - s * per, per});
+    } else {
+#pragma unroll 1
+        for (int s = 0; s < ns; ++s) f(s, Lanes{t, n});
+    }
+}
+
 // ---- y stages: lanes along the columns -----------------------------------------
 
 // inverse, last stage: rows of the global spectrum -> LDS (column 0 repacked:
 // C(ky) = A(ky) + i B(ky) with A(-ky) = conj A(ky), see col0_type)
 template <RadixSet RSY>
-__device__ __forceinline__ void y_load_inv(const XSArgs &a, const Rows &P, float2 *sh, const float2 *S) {
+__device__ __forceinline__ void y_load_inv(const XSArgs &a, const Rows &P, Lanes L, float2 *sh, const float2 *S) {
     const int w = a.ay.wl, ny = P.ny;
     with_radix<RSY>(a.ay.rl, [&](auto RC) __attribute__((always_inline)) {
         constexpr int R = decltype(RC)::value;
         const int nt = P.M * w;
-        for (int i = threadIdx.x; i < nt; i += blockDim.x) {
+        for (int i = L.first; i < nt; i += L.count) {
             const int b = a.dM.div(i), c = i - b * P.M;
             float2 v[R];
 #pragma unroll
@@ -93,12 +117,12 @@ __device__ __forceinline__ void y_load_inv(const XSArgs &a, const Rows &P, float
 
 // stage p in LDS (not the last one)
 template <RadixSet RSY, bool INV>
-__device__ __forceinline__ void y_stage(const XSArgs &a, const Rows &P, float2 *sh, int p) {
+__device__ __forceinline__ void y_stage(const XSArgs &a, const Rows &P, Lanes L, float2 *sh, int p) {
     const int w = pick3(a.ay.w, p);
     with_radix<RSY>(pick3(a.ay.r, p), [&](auto RC) __attribute__((always_inline)) {
         constexpr int R = decltype(RC)::value;
         const int nt = P.M * (P.ny / R);
-        for (int i = threadIdx.x; i < nt; i += blockDim.x) {
+        for (int i = L.first; i < nt; i += L.count) {
             const int t = a.dM.div(i), c = i - t * P.M;
             const int hi = p == 0 ? t : a.ay.dw1.div(t), lo = t - hi * w;
             const int ts = w * digit_index(a.ay, p, hi);
@@ -118,12 +142,12 @@ __device__ __forceinline__ void y_stage(const XSArgs &a, const Rows &P, float2 *
 
 // last forward stage, to the rows of the global spectrum; column 0 stays in LDS
 template <RadixSet RSY>
-__device__ __forceinline__ void y_store(const XSArgs &a, const Rows &P, float2 *sh, float2 *S) {
+__device__ __forceinline__ void y_store(const XSArgs &a, const Rows &P, Lanes L, float2 *sh, float2 *S) {
     const int w = a.ay.wl;
     with_radix<RSY>(a.ay.rl, [&](auto RC) __attribute__((always_inline)) {
         constexpr int R = decltype(RC)::value;
         const int nt = P.M * w;
-        for (int i = threadIdx.x; i < nt; i += blockDim.x) {
+        for (int i = L.first; i < nt; i += L.count) {
             const int b = a.dM.div(i), c = i - b * P.M;
             float2 *const e = sh + b * P.pitch + pcol(a, c);
             const int step = w * P.pitch;
@@ -142,9 +166,9 @@ __device__ __forceinline__ void y_store(const XSArgs &a, const Rows &P, float2 *
     });
 }
 // column 0 unpacked into A (rows 1..h) and B (rows ny-h..ny-1), see col0_type
-__device__ __forceinline__ void y_store_col0(const Rows &P, const float2 *sh, float2 *S) {
+__device__ __forceinline__ void y_store_col0(const Rows &P, Lanes L, const float2 *sh, float2 *S) {
     const int ny = P.ny;
-    for (int r = threadIdx.x; r < ny; r += blockDim.x) {
+    for (int r = L.first; r < ny; r += L.count) {
         const int type = col0_type(r, ny);
         const int j = col0_ky(r, ny);
         float2 v = sh[j * P.pitch];
@@ -170,12 +194,12 @@ __device__ __forceinline__ void y_store_col0(const Rows &P, const float2 *sh, fl
 // w - b + w q wraps only for b = 0: element q of the partner list is then
 // element q + 1 of the butterfly itself.
 template <RadixSet RSP, bool INV>
-__device__ __forceinline__ void x_pair(const XSArgs &a, const Rows &P, float2 *sh) {
+__device__ __forceinline__ void x_pair(const XSArgs &a, const Rows &P, Lanes L, float2 *sh) {
     const int w = a.ax.wl, cw = pcol(a, w);
     with_radix<RSP>(a.ax.rl, [&](auto RC) __attribute__((always_inline)) {
         constexpr int R = decltype(RC)::value;
         const int nt = P.ny * (w / 2 + 1);
-        for (int i = threadIdx.x; i < nt; i += blockDim.x) {
+        for (int i = L.first; i < nt; i += L.count) {
             const int b = a.drows.div(i), row = i - b * P.ny;
             const bool self = b == 0 || 2 * b == w;
             float2 *const e = sh + row * P.pitch;
@@ -237,12 +261,12 @@ __device__ __forceinline__ void x_pair(const XSArgs &a, const Rows &P, float2 *s
 
 // middle stage of a three-stage x axis (p = 1)
 template <RadixSet RSM, bool INV>
-__device__ __forceinline__ void x_stage1(const XSArgs &a, const Rows &P, float2 *sh) {
+__device__ __forceinline__ void x_stage1(const XSArgs &a, const Rows &P, Lanes L, float2 *sh) {
     const int w = a.ax.w[1];
     with_radix<RSM>(a.ax.r[1], [&](auto RC) __attribute__((always_inline)) {
         constexpr int R = decltype(RC)::value;
         const int nt = P.ny * (P.M / R);
-        for (int i = threadIdx.x; i < nt; i += blockDim.x) {
+        for (int i = L.first; i < nt; i += L.count) {
             const int t = a.drows.div(i), row = i - t * P.ny;
             const int hi = a.ax.dw1.div(t), lo = t - hi * w;
             const int ts = w * hi;
@@ -327,16 +351,16 @@ __device__ __forceinline__ void st_run(float *f, const XTask &T, const float2 (&
 }
 
 // rows of a global spectrum to LDS, and the x spectrum back (rows in grid order)
-__device__ __forceinline__ void x_load(const XSArgs &a, const Rows &P, float2 *sh, const float2 *S) {
+__device__ __forceinline__ void x_load(const XSArgs &a, const Rows &P, Lanes L, float2 *sh, const float2 *S) {
     const int nt = P.M * P.rows;
-    for (int i = threadIdx.x; i < nt; i += blockDim.x) {
+    for (int i = L.first; i < nt; i += L.count) {
         const int y = a.dM.div(i), c = i - y * P.M;
         sh[y * P.pitch + pcol(a, c)] = ld_at(S, (uint32_t)i * 8u);
     }
 }
-__device__ __forceinline__ void x_store(const XSArgs &a, const Rows &P, const float2 *sh, float2 *S) {
+__device__ __forceinline__ void x_store(const XSArgs &a, const Rows &P, Lanes L, const float2 *sh, float2 *S) {
     const int nt = P.M * P.rows;
-    for (int i = threadIdx.x; i < nt; i += blockDim.x) {
+    for (int i = L.first; i < nt; i += L.count) {
         const int y = a.dM.div(i), c = i - y * P.M;
         st_at(S, (uint32_t)i * 8u, sh[P.ypos[y] * P.pitch + pcol(a, c)]);
     }
@@ -479,8 +503,7 @@ constexpr RadixSet kAnyP = kPow2P | radix_bit(3) | radix_bit(5) | radix_bit(6) |
                            radix_bit(10) | radix_bit(12);
 
 #define KW_XS_TEMPLATE template <RadixSet RSY, RadixSet RSM, RadixSet RSP, bool PLANES
-// (a density plane block, one to a CU, takes up to 256 registers: at 128 it spilled
-// 200 bytes a thread)
+// (a density plane block takes up to 168 registers: at 128 it spilled 200 bytes a thread)
 #define KW_XS_BOUNDS(PLANE_THREADS, WAVES) __launch_bounds__(PLANES ? PLANE_THREADS : 256, PLANES ? 1 : WAVES)
 #define KW_XS_BEGIN(PY, PZ)                                                    \
     extern __shared__ float2 lds_all[];                                        \
@@ -493,57 +516,48 @@ constexpr RadixSet kAnyP = kPow2P | radix_bit(3) | radix_bit(5) | radix_bit(6) |
 
 // Spectra of NS fields -> the points before the update, set by set (each step's
 // sets between two barriers), and NS sets back to spectra
-KW_XS_TEMPLATE, class Src>
-__device__ __forceinline__ void to_points(const XSArgs &a, const Rows &P, int ns, Src src) {
-#pragma unroll 1
-    for (int s = 0; s < ns; ++s) {
-        if constexpr (PLANES) y_load_inv<RSY>(a, P, P.set(s), src(s));
-        else x_load(a, P, P.set(s), src(s));
-    }
+KW_XS_TEMPLATE, int NS, class Src>
+__device__ __forceinline__ void to_points(const XSArgs &a, const Rows &P, Src src) {
+    constexpr int ns = NS;
+    for_sets<PLANES, NS>(ns, [&](int s, Lanes L) __attribute__((always_inline)) {
+        if constexpr (PLANES) y_load_inv<RSY>(a, P, L, P.set(s), src(s));
+        else x_load(a, P, L, P.set(s), src(s));
+    });
     __syncthreads();
     if constexpr (PLANES) {
 #pragma unroll 1
         for (int p = a.ay.np - 2; p >= 0; --p) {
-#pragma unroll 1
-            for (int s = 0; s < ns; ++s) y_stage<RSY, true>(a, P, P.set(s), p);
+            for_sets<PLANES, NS>(ns, [&](int s, Lanes L) __attribute__((always_inline)) { y_stage<RSY, true>(a, P, L, P.set(s), p); });
             __syncthreads();
         }
     }
-#pragma unroll 1
-    for (int s = 0; s < ns; ++s) x_pair<RSP, true>(a, P, P.set(s));
+    for_sets<PLANES, NS>(ns, [&](int s, Lanes L) __attribute__((always_inline)) { x_pair<RSP, true>(a, P, L, P.set(s)); });
     __syncthreads();
     if (a.ax.np == 3) {
-#pragma unroll 1
-        for (int s = 0; s < ns; ++s) x_stage1<RSM, true>(a, P, P.set(s));
+        for_sets<PLANES, NS>(ns, [&](int s, Lanes L) __attribute__((always_inline)) { x_stage1<RSM, true>(a, P, L, P.set(s)); });
         __syncthreads();
     }
 }
 // SPECTRUM_Y: the y transform too (planes)
-KW_XS_TEMPLATE, bool SPECTRUM_Y, class Dst>
+KW_XS_TEMPLATE, bool SPECTRUM_Y, int NS, class Dst>
 __device__ __forceinline__ void to_spectra(const XSArgs &a, const Rows &P, int ns, Dst dst) {
     if (a.ax.np == 3) {
-#pragma unroll 1
-        for (int s = 0; s < ns; ++s) x_stage1<RSM, false>(a, P, P.set(s));
+        for_sets<PLANES, NS>(ns, [&](int s, Lanes L) __attribute__((always_inline)) { x_stage1<RSM, false>(a, P, L, P.set(s)); });
         __syncthreads();
     }
-#pragma unroll 1
-    for (int s = 0; s < ns; ++s) x_pair<RSP, false>(a, P, P.set(s));
+    for_sets<PLANES, NS>(ns, [&](int s, Lanes L) __attribute__((always_inline)) { x_pair<RSP, false>(a, P, L, P.set(s)); });
     __syncthreads();
     if constexpr (PLANES && SPECTRUM_Y) {
 #pragma unroll 1
         for (int p = 0; p < a.ay.np - 1; ++p) {
-#pragma unroll 1
-            for (int s = 0; s < ns; ++s) y_stage<RSY, false>(a, P, P.set(s), p);
+            for_sets<PLANES, NS>(ns, [&](int s, Lanes L) __attribute__((always_inline)) { y_stage<RSY, false>(a, P, L, P.set(s), p); });
             __syncthreads();
         }
-#pragma unroll 1
-        for (int s = 0; s < ns; ++s) y_store<RSY>(a, P, P.set(s), dst(s));
+        for_sets<PLANES, NS>(ns, [&](int s, Lanes L) __attribute__((always_inline)) { y_store<RSY>(a, P, L, P.set(s), dst(s)); });
         __syncthreads();
-#pragma unroll 1
-        for (int s = 0; s < ns; ++s) y_store_col0(P, P.set(s), dst(s));
+        for_sets<PLANES, NS>(ns, [&](int s, Lanes L) __attribute__((always_inline)) { y_store_col0(P, L, P.set(s), dst(s)); });
     } else {
-#pragma unroll 1
-        for (int s = 0; s < ns; ++s) x_store(a, P, P.set(s), dst(s));
+        for_sets<PLANES, NS>(ns, [&](int s, Lanes L) __attribute__((always_inline)) { x_store(a, P, L, P.set(s), dst(s)); });
     }
 }
 
@@ -554,7 +568,7 @@ KW_XS_TEMPLATE, bool POINTS>
 __global__ void KW_XS_BOUNDS(1024, 4) kw_xvel_s(XSArgs a) {
     KW_XS_BEGIN(pml_sy, pml_sz)
     const int xi = blockIdx.y;
-    to_points<RSY, RSM, RSP, PLANES>(a, P, 1, [&](int) __attribute__((always_inline)) { return pick3(x.Sin, xi) + soff; });
+    to_points<RSY, RSM, RSP, PLANES, 1>(a, P, [&](int) __attribute__((always_inline)) { return pick3(x.Sin, xi) + soff; });
     float *const u = pick3(x.fld, xi);
     const Coef dtr = xi == 0 ? x.m.dtr[0] : xi == 1 ? x.m.dtr[1] : x.m.dtr[2];
     const float *const q_rows = xi == 1 ? P.qy : P.qz;
@@ -597,7 +611,7 @@ __global__ void KW_XS_BOUNDS(1024, 4) kw_xvel_s(XSArgs a) {
             run_forward<R>(P, P.sh + off, j, v);
         });
     }
-    to_spectra<RSY, RSM, RSP, PLANES, true>(a, P, 1, [&](int) __attribute__((always_inline)) { return pick3(x.Sout, xi) + soff; });
+    to_spectra<RSY, RSM, RSP, PLANES, true, 1>(a, P, 1, [&](int) __attribute__((always_inline)) { return pick3(x.Sout, xi) + soff; });
 }
 
 // p = c0^2 rho + nl rho^2 on a task's points (Eq. (6) without absorption)
@@ -641,9 +655,9 @@ __device__ __forceinline__ void den_finish(const XSArgs &a, const Rows &P, float
 // and rho, or the equation of state and the spectrum of p.  Rows with mass source
 // points add them to the stored components between the two transforms.
 KW_XS_TEMPLATE, bool ABS>
-__global__ void KW_XS_BOUNDS(512, 3) kw_xden_s(XSArgs a) {
+__global__ void KW_XS_BOUNDS(768, 3) kw_xden_s(XSArgs a) {
     KW_XS_BEGIN(pml_y, pml_z)
-    to_points<RSY, RSM, RSP, PLANES>(a, P, 3, [&](int g) __attribute__((always_inline)) { return pick3(x.Sin, g) + soff; });
+    to_points<RSY, RSM, RSP, PLANES, 3>(a, P, [&](int g) __attribute__((always_inline)) { return pick3(x.Sin, g) + soff; });
     const bool sumd = ABS && !x.rho0_sum_in_z;
     const bool src = x.src.kind == KW_SOURCE_MASS && rows_have_points(x.src.row_ptr, row0, P.rows);
     const int step = *x.cnt.step;
@@ -726,7 +740,7 @@ __global__ void KW_XS_BOUNDS(512, 3) kw_xden_s(XSArgs a) {
         });
     }
     if constexpr (ABS) {
-        to_spectra<RSY, RSM, RSP, PLANES, true>(a, P, sumd ? 2 : 1, [&](int s) __attribute__((always_inline)) {
+        to_spectra<RSY, RSM, RSP, PLANES, true, 0>(a, P, sumd ? 2 : 1, [&](int s) __attribute__((always_inline)) {
             return (sumd && s == 0 ? x.Sout[0] : x.Sout[1]) + soff;
         });
     } else {
@@ -740,7 +754,7 @@ __global__ void KW_XS_BOUNDS(512, 3) kw_xden_s(XSArgs a) {
                 run_forward<R>(P, P.sh + off, j, p);
             });
         }
-        to_spectra<RSY, RSM, RSP, PLANES, false>(a, P, 1, [&](int) __attribute__((always_inline)) { return x.Sout[0] + soff; });
+        to_spectra<RSY, RSM, RSP, PLANES, false, 1>(a, P, 1, [&](int) __attribute__((always_inline)) { return x.Sout[0] + soff; });
     }
 }
 
@@ -750,7 +764,7 @@ __global__ void KW_XS_BOUNDS(512, 3) kw_xden_s(XSArgs a) {
 KW_XS_TEMPLATE, bool MERGED, bool POINTS>
 __global__ void KW_XS_BOUNDS(1024, 4) kw_xeos_s(XSArgs a) {
     KW_XS_BEGIN(pml_y, pml_z)
-    to_points<RSY, RSM, RSP, PLANES>(a, P, MERGED ? 1 : 2, [&](int s) __attribute__((always_inline)) { return (s ? x.Sin[1] : x.Sin[0]) + soff; });
+    to_points<RSY, RSM, RSP, PLANES, MERGED ? 1 : 2>(a, P, [&](int s) __attribute__((always_inline)) { return (s ? x.Sin[1] : x.Sin[0]) + soff; });
     const int step = *x.cnt.step;
     const bool rec = step >= x.sen.record_start;
     x_middle<RSM>(a, P, roff, [&](auto RC, const XTask &T, int off, int j) __attribute__((always_inline)) {
@@ -794,7 +808,7 @@ __global__ void KW_XS_BOUNDS(1024, 4) kw_xeos_s(XSArgs a) {
             run_forward<R>(P, P.sh + off, j, p);
         });
     }
-    to_spectra<RSY, RSM, RSP, PLANES, false>(a, P, 1, [&](int) __attribute__((always_inline)) { return x.Sout[0] + soff; });
+    to_spectra<RSY, RSM, RSP, PLANES, false, 1>(a, P, 1, [&](int) __attribute__((always_inline)) { return x.Sout[0] + soff; });
 }
 
 }  // namespace
