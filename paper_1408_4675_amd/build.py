@@ -35,7 +35,7 @@ def _run(cmd):
     return r.stdout
 
 
-HIP_SOURCES = ("kernels_yz.hip", "kernels_zs.hip", "kernels_ys.hip", "kernels_x.hip", "kernels_xs.hip", "kernels_xs2.hip", "kernels_util.hip", "kernels_adj.hip",
+HIP_SOURCES = ("kernels_yz.hip", "kernels_zs.hip", "kernels_ys.hip", "kernels_x.hip", "kernels_xs.hip", "kernels_xs2.hip", "kernels_xadj.hip", "kernels_util.hip", "kernels_adj.hip",
                "static_scratch.hip")
 PROBE_SOURCES = ("zcol_copy.hip",)
 

@@ -393,7 +393,7 @@ void pick_ystaged(const GridDev &g, size_t max_lds, LaunchCfg &c) {
 // their blocks
 void pick_xstaged(const GridDev &g, bool absorbing, bool merged, size_t max_lds, LaunchCfg &c) {
     c.xs = 0;
-    c.xs_passes = c.planes = 0;
+    c.xs_passes = c.planes = c.xs_adj = 0;
     const bool row_pow2 = is_pow2(g.M), pow2 = row_pow2 && is_pow2(g.ny);
     auto layout = [&](bool p2) {
         if (!stage_axis(g.M, ST_ROW, p2, c.xs_axis)) return false;
@@ -461,6 +461,29 @@ void pick_xstaged(const GridDev &g, bool absorbing, bool merged, size_t max_lds,
         c.xs_passes |= 1u << p;
     }
     if (c.xs_passes) c.xs = set ? 1 : 2;
+    if (c.xs_passes >> XS_VEL & 1) c.xs_adj = 1u << ADJX_VEL;
+    // The reverse passes, on the rows of the pressure pass (two sets) and of the density
+    // pass (three sets): the equation of state wherever those run on rows; the density
+    // where the engine idles half its threads (its update streams fifteen fields, which the
+    // engine's smaller blocks overlap better); the sum there and with two stages.
+    // us, rows : engine, density / sum / equation of state: 250 x 135 x 90 (125 = 5 25)
+    // 143 : 357 / 21 : 112 / 41 : 155; 100 x 162 x 243 (50 = 5 10) 163 : 198 / 32 : 47 / 54 :
+    // 87; 150 x 128 x 64 (75 = 5 15) 64 : 63 / 14 : 21 / 21 : 33; 160^3 (80 = 8 10) 190 : 201 /
+    // 31 : 37 / 57 : 60; 360 x 270 x 120 (180 = 12 15) 575 : 424 / 85 : 78 / 154 : 171
+    const unsigned on_rows = c.xs_passes & ~c.planes;
+    int rmin = INT_MAX, rmax = 0;
+    for (int i = 0; i < c.px.np; ++i) {
+        rmin = std::min(rmin, c.px.radix[i]);
+        rmax = std::max(rmax, c.px.radix[i]);
+    }
+    const bool uneven = rmax >= 2 * rmin;
+    if (on_rows >> XS_EOS & 1 && xs_lds_bytes(g.M, 0, c.xs_rows[XS_EOS], 2, c.xs_pitch) <= max_lds)
+        c.xs_adj |= 1u << ADJX_EOS;
+    if (on_rows >> XS_DEN & 1) {
+        if (uneven || c.xs_axis.np == 2) c.xs_adj |= 1u << ADJX_SUM;
+        if (uneven && xs_lds_bytes(g.M, 0, c.xs_rows[XS_DEN], 3, c.xs_pitch) + xs_mask_bytes(g.nx, c.xs_rows[XS_DEN]) <= max_lds)
+            c.xs_adj |= 1u << ADJX_DEN | 1u << ADJX_DEN_ABS;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1049,7 +1072,7 @@ int pick_tiles(kw_sim *s, int tile_y, int tile_z) {
     if (s->zs_off) c.zs = 0;
     pick_ystaged(g, s->max_lds, c);
     pick_xstaged(g, s->med.absorbing, s->merged_abs, s->max_lds, c);
-    if (s->xy_off) c.ys = c.xs_passes = c.planes = 0;
+    if (s->xy_off) c.ys = c.xs_passes = c.planes = c.xs_adj = 0;
     // the column passes address an element of their tile by a 32-bit byte offset
     const uint64_t zlane = ((uint64_t)std::max(c.pz.L, c.pza.L) * g.M * g.ny + std::max(c.tb_z, c.tb_za)) * 8;
     if (zlane >= (1ull << 32))
@@ -2147,10 +2170,13 @@ int reverse_step(kw_adj *adj, int n, const char *rec) {
     float2 *const *S = s->buf.S;
     float2 *s12[2] = {S[1], S[2]}, *s45[2] = {S[4], S[5]};
     float2 *s123[3] = {S[1], S[2], S[3]}, *s456[3] = {S[4], S[5], S[6]};
+    // (a velocity pass on planes transforms its spectra along y itself)
+    const bool planes = c.planes >> XS_VEL & 1;
     auto yzy = [&](int mode, float2 *const *in, float2 *const *out, int k) -> hipError_t {
-        hipError_t r = launch_ypass(st, g, c, t, in, k, false, nullptr, nullptr);
+        hipError_t r = hipSuccess;
+        if (!(planes && mode == ZM_GRADT)) r = launch_ypass(st, g, c, t, in, k, false, nullptr, nullptr);
         if (r == hipSuccess) r = launch_zfused(st, g, c, t, mode, in, out);
-        if (r == hipSuccess) r = launch_ypass(st, g, c, t, out, k, true, nullptr, nullptr);
+        if (r == hipSuccess && !(planes && mode == ZM_DIVT)) r = launch_ypass(st, g, c, t, out, k, true, nullptr, nullptr);
         return r;
     };
     KW_A(launch_adj_src(st, a, s->src, n));

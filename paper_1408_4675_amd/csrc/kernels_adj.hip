@@ -25,8 +25,10 @@
 // Each line is one x-row kernel: the inverse x transforms of its spectral
 // inputs, the point-wise update, the forward x transforms of its spectral
 // outputs (kw_adjx_eos, kw_adjx_den, kw_adjx_vel, kw_adjx_sum), as in the
-// forward step's x passes.
+// forward step's x passes.  Where those run on staged transforms these do too
+// (kernels_xadj.hip).
 #include "kernels_impl.h"
+#include "xstaged.h"
 
 namespace kw {
 
@@ -387,6 +389,7 @@ hipError_t launch_adjx(hipStream_t s, int pass, const GridDev &g, const LaunchCf
         a.Sin[i] = Sin ? Sin[i] : nullptr;
         a.Sout[i] = Sout ? Sout[i] : nullptr;
     }
+    if (c.xs_adj >> pass & 1) return launch_xs_adj(s, pass, c, a, ad, p_spec, loss);
     const int L = loss ? 1 : 0;
     dim3 grid((g.rows + c.tb_x - 1) / c.tb_x, pass == ADJX_VEL ? 3 : 1);
     dim3 block(c.tb_x * c.px.L);

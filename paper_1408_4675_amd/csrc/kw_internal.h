@@ -185,6 +185,9 @@ inline size_t xs_lds_bytes(int M, int nyt, int rows, int sets, int pitch) {
     return 8 * ((size_t)xs_table_slots(M, nyt, rows) + (size_t)sets * rows * pitch);
 }
 
+// bits of the points of a block's rows (reverse density pass)
+inline size_t xs_mask_bytes(int nx, int rows) { return (size_t)rows * ((nx + 31) / 32) * 4; }
+
 enum { XS_VEL = 0, XS_DEN = 1, XS_EOS = 2 };   // the x passes of a step
 
 struct LaunchCfg {
@@ -204,6 +207,7 @@ struct LaunchCfg {
     // y transforms included; rows of a set in a block, LDS row layout (see pcol)
     int xs;
     unsigned xs_passes, planes;
+    unsigned xs_adj;         // reverse passes on staged transforms, bit 1 << ADJX_*
     int xs_rows[3], xs_pad, xs_pitch, planes_threads[3];
     StageAxis xs_axis, planes_y;
     int zs;                  // z pass on staged transforms (kernels_zs.hip): 0 no, 1 the

@@ -21,5 +21,8 @@ hipError_t launch_xs2_vel(hipStream_t s, const LaunchCfg &c, const XArgs &a, boo
 hipError_t launch_xs2_den(hipStream_t s, const LaunchCfg &c, const XArgs &a, float *scr);
 hipError_t launch_xs2_eos(hipStream_t s, const LaunchCfg &c, const XArgs &a, float *scr,
                           bool points, bool merged);
+// the x passes of a reverse step in LaunchCfg::xs_adj (kernels_xadj.hip)
+hipError_t launch_xs_adj(hipStream_t s, int pass, const LaunchCfg &c, const XArgs &a, const AdjDev &ad,
+                         const float2 *p_spec, bool loss);
 
 }  // namespace kw

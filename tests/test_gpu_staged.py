@@ -93,6 +93,25 @@ def test_reverse_step(kw, shape):
     assert e <= TOL
 
 
+# rows of a generic length (two and three stages, one, a remainder of rows), the velocity
+# pass on planes or, with few large ones, on rows; and planes alone
+@pytest.mark.parametrize("shape", [(250, 20, 10), (250, 36, 6), (810, 6, 8), (90, 48, 15), (128, 36, 8), (64, 12, 9)])
+@pytest.mark.parametrize("absorbing", [True, False])
+def test_reverse_x_passes(kw, shape, absorbing):
+    """The reverse x passes on staged rows and planes, with and without absorption."""
+    from paper_1408_4675_amd.adjoint import focus_gradient
+    scen = sc.small_case(*shape, seed=4, pml=2, steps=6, amp=2.0e6, n_elements=3, absorbing=absorbing)
+    scen = scen.replace(sensor=sc.Sensor(record=sc.REC_INTENSITY, record_start=3))
+    w = np.random.default_rng(6).standard_normal(scen.grid.npts)
+    ref = AdjointOracle(scen, w, workers=4)
+    ref.forward()
+    gr = ref.backward()
+    out = focus_gradient(scen, w, checkpoint_every=3)
+    e = np.linalg.norm(out["source_gradient"] - gr["dJds"]) / np.linalg.norm(gr["dJds"])
+    print("[case] %s dJ/ds %.2e" % (scen.name, e), flush=True)
+    assert e <= TOL
+
+
 def _smooth(n):
     while True:
         m = n
