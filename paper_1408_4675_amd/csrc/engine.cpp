@@ -414,8 +414,8 @@ void pick_xstaged(const GridDev &g, bool absorbing, bool merged, size_t max_lds,
     unsigned planes = g.M * g.ny <= 2048 ? 7u : 3 * g.nz >= 144 || g.M * g.ny <= 4096 ? 1u << XS_VEL : 0u;
     // Rows: the lengths of the generic engine, whose passes of a smaller radix than its
     // largest leave threads idle: us, rows : engine, velocity / density / pressure
-    // 250 x 135 x 90 (125 = 5 25) 53 : 150 / 68 : 249 / 45 : 148; 160^3 63 : 76 / 90 : 91 /
-    // 57 : 60; 360 x 270 x 120 175 : 189 / 264 : 289 / 168 : 164; 450 x 480 x 324 989 : 1061 /
+    // 250 x 135 x 90 (125 = 5 25) 53 : 150 / 68 : 249 / 45 : 148; 160^3 63 : 76 / 86 : 91 /
+    // 54 : 60; 360 x 270 x 120 175 : 189 / 264 : 289 / 168 : 164; 450 x 480 x 324 989 : 1061 /
     // 1512 : 1686 / 522 : 540.  The 8- and 12-wide engines keep theirs (256^3 density
     // 388 : 193, 192^3 158 : 145, 96^3 32 : 28)
     const unsigned rows = eng_fixed(c.eng_x) ? 0u : 7u;

@@ -19,7 +19,7 @@
 // butterfly a thread; density with its three components exchanged through LDS) and now:
 // 250 x 135 x 90 velocity with its y passes 224 -> 92 (planes; 3.0 M points, 15 fields in
 // and out), density 249 -> 62 (2.6 TB/s), pressure 148 -> 45 (3.3 TB/s); 160^3 velocity
-// with its y passes 127 -> 83 (3.0 TB/s), density 91 -> 90, pressure 60 -> 57; 450 x 480 x
+// with its y passes 127 -> 83 (3.0 TB/s), density 91 -> 86, pressure 60 -> 54; 450 x 480 x
 // 324 density 1686 -> 1309, lossless density with the equation of state 2447 -> 1543;
 // 128^3 velocity with its y passes 51 -> 36.
 #pragma once
