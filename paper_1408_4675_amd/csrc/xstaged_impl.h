@@ -469,7 +469,9 @@ __device__ __forceinline__ void pressure_points(const XSArgs &a, const Rows &P, 
     __syncthreads();
     if (x.src.kind == KW_SOURCE_PRESSURE && rows_have_points(x.src.row_ptr, row0, ny)) {
         for_points(x.src.row_ptr, row0, ny, [&](int e, int row) __attribute__((always_inline)) {
-            p[(size_t)row * nx + x.src.xpos[e]] = x.src.coef[e] * x.src.drive[x.src.elem[e]];
+            // (a drive of NaN leaves the pressure as it is, as in finish_pressure)
+            const float v = x.src.coef[e] * x.src.drive[x.src.elem[e]];
+            if (v == v) p[(size_t)row * nx + x.src.xpos[e]] = v;
         });
         __syncthreads();
     }

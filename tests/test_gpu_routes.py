@@ -1,0 +1,64 @@
+"""The same call on the staged passes and on the engines (forced with
+Simulation.set_plan) where the two could answer differently.
+
+Tolerance: that of the staged passes' own tests, 1e-7 * 12 * sqrt(14 * 4) = 9e-6
+for 4 steps of 14 float32 transforms, with a factor two: 2e-5."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_1408_4675_amd import scenarios as sc
+
+pytestmark = pytest.mark.gpu
+
+TOL = 2e-5
+STEPS = 4
+
+
+@pytest.fixture(scope="module")
+def kw():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1408_4675_amd import _abi as A
+    from paper_1408_4675_amd.simulation import Simulation
+    A.load()
+    return A, Simulation
+
+
+def _case(nx, ny, nz, medium, mask=False):
+    return sc.small_case(nx, ny, nz, seed=nx + 7 * ny + 31 * nz, heterogeneous=medium == "maps",
+                         nonlinear=medium != "lossless", absorbing=medium != "lossless", pml=1,
+                         steps=STEPS, sensor_mask=mask)
+
+
+def _same(a, b):
+    a, b = np.asarray(a, np.float64), np.asarray(b, np.float64)
+    assert np.isfinite(a).all()
+    assert np.linalg.norm(a - b) <= TOL * np.linalg.norm(b)
+
+
+# planes and rows for the x passes
+@pytest.mark.parametrize("shape", [(30, 8, 6), (100, 90, 4)], ids=["planes", "rows"])
+@pytest.mark.parametrize("medium", ["maps", "water", "lossless"])
+def test_pressure_source_without_a_value(kw, shape, medium):
+    """A NaN sample of a pressure source's signal imposes nothing in that step."""
+    A, Simulation = kw
+    scen = _case(*shape, medium, mask=True)
+    signal = np.linspace(0.5e6, 1.0e6, STEPS, dtype=np.float32)[None].copy()
+    signal[0, 1] = np.nan
+    scen = scen.replace(source=dataclasses.replace(scen.source, kind=sc.SOURCE_PRESSURE, signal=signal))
+    print("\n[case] %s" % scen.name, flush=True)
+    outs = []
+    for forced in (False, True):
+        sim = Simulation(scen, tune=False)
+        if forced:
+            for axis in range(3):
+                sim.set_plan(axis, None)
+        sim.step(STEPS)
+        assert sim.stats()["nonfinite_step"] == -1
+        outs.append([sim.gather(w, device=False) for w in (A.KW_REC_P_FINAL, A.KW_REC_P_SERIES)])
+        sim.close()
+    for staged, engine in zip(*outs):
+        _same(staged, engine)
