@@ -372,13 +372,13 @@ void pick_zstaged(const GridDev &g, double kx_max, double ky_max, double kz_max,
     c.zs = pow2 ? 1 : 2;
 }
 
-// Whether the y pass runs on staged transforms, and its tiles: the lengths of
-// the generic engine (the fixed-width engines' single-purpose kernels measured
-// equal or faster on theirs)
-void pick_ystaged(const GridDev &g, size_t max_lds, LaunchCfg &c) {
+// Whether the y pass runs on staged transforms, and its tiles: the lengths whose
+// default (eng0) is the generic engine (the fixed-width engines' single-purpose
+// kernels measured equal or faster on theirs)
+void pick_ystaged(const GridDev &g, int eng0, size_t max_lds, LaunchCfg &c) {
     const int n = g.ny;
     c.ys = 0;
-    if (eng_fixed(c.eng_y) || !stage_axis(n, ST_COLUMN, false, c.ys_axis)) return;
+    if (eng_fixed(eng0) || !stage_axis(n, ST_COLUMN, false, c.ys_axis)) return;
     auto lds = [&](int tb) { return 8 * ((size_t)n + (size_t)n * tb); };
     int tb = 16;
     while (tb > 1 && lds(tb) > 80 * 1024) tb /= 2;
@@ -390,8 +390,9 @@ void pick_ystaged(const GridDev &g, size_t max_lds, LaunchCfg &c) {
 }
 
 // Which x passes of a step run on staged transforms, which of them on z planes, and
-// their blocks
-void pick_xstaged(const GridDev &g, bool absorbing, bool merged, size_t max_lds, LaunchCfg &c) {
+// their blocks.  eng0, plan0: the rows' default engine and plan
+void pick_xstaged(const GridDev &g, int eng0, const FftPlan &plan0, bool absorbing, bool merged, size_t max_lds,
+                  LaunchCfg &c) {
     c.xs = 0;
     c.xs_passes = c.planes = c.xs_adj = 0;
     const bool row_pow2 = is_pow2(g.M), pow2 = row_pow2 && is_pow2(g.ny);
@@ -418,7 +419,7 @@ void pick_xstaged(const GridDev &g, bool absorbing, bool merged, size_t max_lds,
     // 54 : 60; 360 x 270 x 120 175 : 189 / 264 : 289 / 168 : 164; 450 x 480 x 324 989 : 1061 /
     // 1512 : 1686 / 522 : 540.  The 8- and 12-wide engines keep theirs (256^3 density
     // 388 : 193, 192^3 158 : 145, 96^3 32 : 28)
-    const unsigned rows = eng_fixed(c.eng_x) ? 0u : 7u;
+    const unsigned rows = eng_fixed(eng0) ? 0u : 7u;
     bool set = pow2;
     if (planes && layout(pow2) && stage_axis(g.ny, ST_PLANE, pow2, c.planes_y)) {
         for (int p = 0; p < passes; ++p) {
@@ -472,9 +473,9 @@ void pick_xstaged(const GridDev &g, bool absorbing, bool merged, size_t max_lds,
     // 31 : 37 / 57 : 60; 360 x 270 x 120 (180 = 12 15) 575 : 424 / 85 : 78 / 154 : 171
     const unsigned on_rows = c.xs_passes & ~c.planes;
     int rmin = INT_MAX, rmax = 0;
-    for (int i = 0; i < c.px.np; ++i) {
-        rmin = std::min(rmin, c.px.radix[i]);
-        rmax = std::max(rmax, c.px.radix[i]);
+    for (int i = 0; i < plan0.np; ++i) {
+        rmin = std::min(rmin, plan0.radix[i]);
+        rmax = std::max(rmax, plan0.radix[i]);
     }
     const bool uneven = rmax >= 2 * rmin;
     if (on_rows >> XS_EOS & 1 && xs_lds_bytes(g.M, 0, c.xs_rows[XS_EOS], 2, c.xs_pitch) <= max_lds)
@@ -760,6 +761,9 @@ struct kw_sim {
     std::vector<Rec> recs;
     std::vector<hipEvent_t> pool;
     size_t max_lds = 64 * 1024;        // LDS bytes a block may use on this device
+    int eng0_x, eng0_y;                // the engines and the x plan that the lengths have
+    FftPlan px0;                       // by default: a hinted schedule (kw_suggest_plan)
+                                       // does not move the staged passes
     bool xy_off = false;            // the caller chose x or y schedules (kw_set_plan)
     bool zs_off = false;               // and the z schedule
     bool merged_abs = false;           // absorption terms merged (scalar c0^2 tau, c0^2 eta)
@@ -1070,8 +1074,8 @@ int pick_tiles(kw_sim *s, int tile_y, int tile_z) {
     }
     pick_zstaged(g, kPi / s->grid.dx, kPi / s->grid.dy, kPi / s->grid.dz, s->max_lds, c);
     if (s->zs_off) c.zs = 0;
-    pick_ystaged(g, s->max_lds, c);
-    pick_xstaged(g, s->med.absorbing, s->merged_abs, s->max_lds, c);
+    pick_ystaged(g, s->eng0_y, s->max_lds, c);
+    pick_xstaged(g, s->eng0_x, s->px0, s->med.absorbing, s->merged_abs, s->max_lds, c);
     if (s->xy_off) c.ys = c.xs_passes = c.planes = c.xs_adj = 0;
     // the column passes address an element of their tile by a 32-bit byte offset
     const uint64_t zlane = ((uint64_t)std::max(c.pz.L, c.pza.L) * g.M * g.ny + std::max(c.tb_z, c.tb_za)) * 8;
@@ -1150,6 +1154,9 @@ int prepare(const kw_grid *grid, const kw_medium *medium, const kw_source *sourc
     s->L = L;
     s->cnt = cnt;
     s->cfg = cfg;
+    s->eng0_x = cfg.eng_x;
+    s->eng0_y = cfg.eng_y;
+    s->px0 = cfg.px;
     s->dt = dt;
     s->c_ref = c_ref;
     s->record_start = sensor ? sensor->record_start : 1;

@@ -62,3 +62,27 @@ def test_pressure_source_without_a_value(kw, shape, medium):
         sim.close()
     for staged, engine in zip(*outs):
         _same(staged, engine)
+
+
+@pytest.mark.parametrize("shape,axis,radices", [((40, 100, 12), 1, [10, 10]), ((200, 90, 20), 0, [10, 10])])
+def test_a_hint_changes_no_bit(kw, shape, axis, radices):
+    """Passes on staged transforms run as they would without the hint, bit by bit; the same
+    schedule forced runs on the engine, to other last bits.  (p_max and u are written by the
+    passes of the step; the gathered pressure goes through an engine's inverse transform.)"""
+    A, Simulation = kw
+    scen = _case(*shape, "maps")
+    print("\n[case] %s axis %d" % (scen.name, axis), flush=True)
+    outs = []
+    for call in (None, "kw_suggest_plan", "kw_set_plan"):
+        sim = Simulation(scen, tune=False)
+        if call:
+            sim._plan(getattr(sim.lib, call), axis, radices, 0)
+        sim.step(STEPS)
+        outs.append(np.concatenate([sim.gather(w, device=False).ravel() for w in (A.KW_REC_P_MAX, A.KW_REC_U_FINAL)]))
+        sim.close()
+    staged, hinted, forced = outs
+    assert np.array_equal(hinted, staged)
+    assert not np.array_equal(forced, staged)
+    n = scen.grid.npts
+    for i in range(4):                                       # p_max, u_x, u_y, u_z
+        _same(forced[i * n:(i + 1) * n], staged[i * n:(i + 1) * n])
