@@ -279,9 +279,11 @@ int kw_set_graph(kw_sim *sim, int32_t steps_per_graph);
  * left as it was), KW_ESTATE after the first step. */
 int kw_set_plan(kw_sim *sim, int axis, const int32_t *radices, int32_t n_radices,
                 int32_t tile);
-/* The same, as a hint: lengths whose passes run on staged transforms with
- * schedules of their own go on doing so (kw_set_plan makes them run on the
- * engines, on the schedule it sets).  The hint serves the other passes. */
+/* The same, as a hint: passes that run on staged transforms, with schedules of
+ * their own, go on doing so (kw_set_plan makes the passes of its axis run on
+ * the engines, on the schedule it sets, and leaves those of the other axes;
+ * x passes that take the y transforms in do so on the default of both axes
+ * only).  The hint serves the other passes. */
 int kw_suggest_plan(kw_sim *sim, int axis, const int32_t *radices, int32_t n_radices,
                     int32_t tile);
 

@@ -390,9 +390,10 @@ void pick_ystaged(const GridDev &g, int eng0, size_t max_lds, LaunchCfg &c) {
 }
 
 // Which x passes of a step run on staged transforms, which of them on z planes, and
-// their blocks.  eng0, plan0: the rows' default engine and plan
-void pick_xstaged(const GridDev &g, int eng0, const FftPlan &plan0, bool absorbing, bool merged, size_t max_lds,
-                  LaunchCfg &c) {
+// their blocks.  eng0, plan0: the rows' default engine and plan; on_planes: whether the y
+// transforms may be part of them
+void pick_xstaged(const GridDev &g, int eng0, const FftPlan &plan0, bool absorbing, bool merged, bool on_planes,
+                  size_t max_lds, LaunchCfg &c) {
     c.xs = 0;
     c.xs_passes = c.planes = c.xs_adj = 0;
     const bool row_pow2 = is_pow2(g.M), pow2 = row_pow2 && is_pow2(g.ny);
@@ -413,6 +414,7 @@ void pick_xstaged(const GridDev &g, int eng0, const FftPlan &plan0, bool absorbi
     // pressure with the y passes that they take in, 48 x 20 x 18 34 : 56, 64^3 47 : 57, but
     // 96^3 87 : 82
     unsigned planes = g.M * g.ny <= 2048 ? 7u : 3 * g.nz >= 144 || g.M * g.ny <= 4096 ? 1u << XS_VEL : 0u;
+    if (!on_planes) planes = 0;
     // Rows: the lengths of the generic engine, whose passes of a smaller radix than its
     // largest leave threads idle: us, rows : engine, velocity / density / pressure
     // 250 x 135 x 90 (125 = 5 25) 53 : 150 / 68 : 249 / 45 : 148; 160^3 63 : 76 / 86 : 91 /
@@ -764,8 +766,8 @@ struct kw_sim {
     int eng0_x, eng0_y;                // the engines and the x plan that the lengths have
     FftPlan px0;                       // by default: a hinted schedule (kw_suggest_plan)
                                        // does not move the staged passes
-    bool xy_off = false;            // the caller chose x or y schedules (kw_set_plan)
-    bool zs_off = false;               // and the z schedule
+    bool engines[3] = {};              // axes whose schedule the caller chose (kw_set_plan):
+                                       // their passes run on the engines
     bool merged_abs = false;           // absorption terms merged (scalar c0^2 tau, c0^2 eta)
     bool rho0_sum_in_z = false;        // absorbing with a constant rho0: the divergence
                                        // pass forms the spectrum of rho0 sum du
@@ -1073,10 +1075,11 @@ int pick_tiles(kw_sim *s, int tile_y, int tile_z) {
         }
     }
     pick_zstaged(g, kPi / s->grid.dx, kPi / s->grid.dy, kPi / s->grid.dz, s->max_lds, c);
-    if (s->zs_off) c.zs = 0;
+    if (s->engines[2]) c.zs = 0;
     pick_ystaged(g, s->eng0_y, s->max_lds, c);
-    pick_xstaged(g, s->eng0_x, s->px0, s->med.absorbing, s->merged_abs, s->max_lds, c);
-    if (s->xy_off) c.ys = c.xs_passes = c.planes = c.xs_adj = 0;
+    if (s->engines[1]) c.ys = 0;
+    pick_xstaged(g, s->eng0_x, s->px0, s->med.absorbing, s->merged_abs, !s->engines[1], s->max_lds, c);
+    if (s->engines[0]) c.xs_passes = c.planes = c.xs_adj = 0;
     // the column passes address an element of their tile by a 32-bit byte offset
     const uint64_t zlane = ((uint64_t)std::max(c.pz.L, c.pza.L) * g.M * g.ny + std::max(c.tb_z, c.tb_za)) * 8;
     if (zlane >= (1ull << 32))
@@ -1840,16 +1843,15 @@ static int apply_plan(kw_sim *s, int axis, const int32_t *radices, int32_t n_rad
     if (axis < 0 || axis > 2) return fail(KW_EINVAL, "axis must be 0, 1 or 2");
     if (s->stepped) return fail(KW_ESTATE, "plans are fixed after the first step");
     LaunchCfg save = s->cfg;
-    const bool save_off = s->xy_off, save_zs_off = s->zs_off;
-    if (!hint) (axis < 2 ? s->xy_off : s->zs_off) = true;
+    const bool was_engines = s->engines[axis];
+    if (!hint) s->engines[axis] = true;
     const int n = axis == 0 ? s->g.M : axis == 1 ? s->g.ny : s->g.nz;
     if (radices && n_radices > 0) {
         std::vector<int> rad(radices, radices + n_radices);
         FftPlan f, r;
         int eng;
         if (!axis_plan(n, axis, &rad, eng, f, r)) {
-            s->xy_off = save_off;
-            s->zs_off = save_zs_off;
+            s->engines[axis] = was_engines;
             return fail(KW_EINVAL, "radices do not form a schedule for length %d", n);
         }
         (axis == 0 ? s->cfg.px : axis == 1 ? s->cfg.py : s->cfg.pz) = f;
@@ -1863,8 +1865,7 @@ static int apply_plan(kw_sim *s, int axis, const int32_t *radices, int32_t n_rad
     }
     if (rc != KW_OK) {
         s->cfg = save;
-        s->xy_off = save_off;
-        s->zs_off = save_zs_off;
+        s->engines[axis] = was_engines;
         return rc;
     }
     drop_graph(s);

@@ -55,3 +55,25 @@ def test_a_hint_leaves_staged_passes(route, shape, hint, medium):
     assert want["ys"] or want["xs_passes"]
     assert got["status"] == [0]
     assert {k: got[k] for k in STAGED} == {k: want[k] for k in STAGED}
+
+
+# an axis' own passes go to the engines, those of the others stay: x rows and a staged y
+# pass (generic lengths), planes (two axes in one pass), powers of two
+@pytest.mark.parametrize("shape", [(250, 135, 20), (100, 90, 12), (30, 8, 6), (64, 64, 48), (128, 36, 30)])
+@pytest.mark.parametrize("medium", ["maps", "lossless"])
+def test_a_forced_axis_leaves_the_others(route, shape, medium):
+    want = route(shape, medium)
+    for axis in range(3):
+        got = route(shape, medium, "set:%d::0" % axis)
+        assert got["status"] == [0]
+        assert got["zs"] == (0 if axis == 2 else want["zs"])
+        assert got["ys"] == (0 if axis == 1 else want["ys"])
+        if axis == 2:
+            assert {k: got[k] for k in STAGED[1:]} == {k: want[k] for k in STAGED[1:]}
+            continue
+        assert got["planes"] == 0
+        rows = want["eng_x"] < 2 and axis == 1                 # generic x lengths have rows
+        assert bool(got["xs_passes"]) == rows
+    # a refused schedule changes nothing
+    got = route(shape, medium, "set:1:7,11:0")
+    assert got["status"] != [0] and {k: got[k] for k in STAGED} == {k: want[k] for k in STAGED}

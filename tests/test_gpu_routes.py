@@ -86,3 +86,24 @@ def test_a_hint_changes_no_bit(kw, shape, axis, radices):
     n = scen.grid.npts
     for i in range(4):                                       # p_max, u_x, u_y, u_z
         _same(forced[i * n:(i + 1) * n], staged[i * n:(i + 1) * n])
+
+
+@pytest.mark.parametrize("shape", [(30, 8, 6), (100, 90, 4), (64, 64, 48)])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_one_axis_on_the_engines(kw, shape, axis):
+    """One axis' passes forced to the engines, those of the others as they were (x passes on
+    planes need two): the same fields."""
+    A, Simulation = kw
+    scen = _case(*shape, "maps")
+    print("\n[case] %s axis %d" % (scen.name, axis), flush=True)
+    outs = []
+    for forced in (False, True):
+        sim = Simulation(scen, tune=False)
+        if forced:
+            sim.set_plan(axis, None)
+        sim.step(STEPS)
+        outs.append([sim.gather(w, device=False) for w in (A.KW_REC_P_FINAL, A.KW_REC_P_MAX)] +
+                    list(sim.gather(A.KW_REC_U_FINAL, device=False).reshape(3, -1)))
+        sim.close()
+    for staged, mixed in zip(*outs):
+        _same(mixed, staged)
