@@ -287,6 +287,12 @@ int kw_set_plan(kw_sim *sim, int axis, const int32_t *radices, int32_t n_radices
 int kw_suggest_plan(kw_sim *sim, int axis, const int32_t *radices, int32_t n_radices,
                     int32_t tile);
 
+/* Where the passes of a step run, by kernel class (in kw_stats' order): bits 0..7
+ * on the FFT engines (kw_set_plan's schedules), bits 8..15 on staged transforms;
+ * bits 16..18: the velocity, density and pressure x passes that take the y
+ * transforms around them in.  Classes without a launch have no bit.  0 for NULL. */
+uint32_t kw_routes(const kw_sim *sim);
+
 /* State snapshots (checkpoint / restart, Section 3.4: a run can be stopped
  * and resumed from its saved state).  A snapshot holds the step counter, the
  * non-finite flag, u_x, u_y, u_z, rho_x, rho_y, rho_z, the pressure (as its

@@ -45,10 +45,13 @@ KW_FIELD_RHOY = 6
 KW_FIELD_RHOZ = 7
 
 # every symbol include/kw.h declares
+# kernel classes of a step, in the order of kw_stats and of the bits of kw_routes
+KERNEL_CLASSES = ("ypass_fwd", "ypass_inv", "zfused_grad", "zfused_div", "zfused_abs", "xvel", "xden", "xeos")
+
 EXPORTS = ("kw_workspace_size", "kw_create", "kw_prepare", "kw_plan_workspace_size",
            "kw_create_prepared", "kw_plan_destroy", "kw_create_static", "kw_step", "kw_gather", "kw_gather_bytes",
            "kw_set_field", "kw_gather_field", "kw_profile", "kw_stats", "kw_set_graph",
-           "kw_set_plan", "kw_suggest_plan", "kw_state_bytes", "kw_save", "kw_load", "kw_adjoint_workspace_size",
+           "kw_set_plan", "kw_suggest_plan", "kw_routes", "kw_state_bytes", "kw_save", "kw_load", "kw_adjoint_workspace_size",
            "kw_adjoint_create", "kw_adjoint_objective", "kw_adjoint_step", "kw_adjoint_source_gradient",
            "kw_adjoint_record_bytes", "kw_adjoint_record", "kw_adjoint_step_record",
            "kw_adjoint_gradient", "kw_adjoint_destroy", "kw_destroy", "kw_last_error")
@@ -158,6 +161,8 @@ def _load(path):
     lib.kw_set_plan.argtypes = [C.c_void_p, C.c_int, P(C.c_int32), C.c_int32, C.c_int32]
     lib.kw_suggest_plan.restype = C.c_int
     lib.kw_suggest_plan.argtypes = lib.kw_set_plan.argtypes
+    lib.kw_routes.restype = C.c_uint32
+    lib.kw_routes.argtypes = [C.c_void_p]
     lib.kw_state_bytes.restype = C.c_int64
     lib.kw_state_bytes.argtypes = [C.c_void_p]
     lib.kw_save.restype = C.c_int

@@ -1880,6 +1880,25 @@ int kw_suggest_plan(kw_sim *s, int axis, const int32_t *radices, int32_t n_radic
     return apply_plan(s, axis, radices, n_radices, tile, true);
 }
 
+uint32_t kw_routes(const kw_sim *s) {
+    if (!s) return 0;
+    const LaunchCfg &c = s->cfg;
+    const bool absorbing = s->med.absorbing;
+    uint32_t engines = 0, staged = 0;
+    auto add = [&](int cls, bool st) { (st ? staged : engines) |= 1u << cls; };
+    auto zs = [&](int mode) { return c.zs && !(c.zs_skip >> mode & 1); };
+    add(KC_YFWD, c.ys);                                  // (the first pass of every step)
+    const unsigned all = absorbing ? 7u : 1u << XS_VEL | 1u << XS_DEN;
+    if ((c.planes & all) != all) add(KC_YINV, c.ys);
+    add(KC_ZGRAD, zs(ZM_GRAD));
+    add(KC_ZDIV, zs(ZM_DIV));
+    if (absorbing) add(KC_ZABS, zs(s->merged_abs ? ZM_ABSM : ZM_ABS));
+    add(KC_XVEL, c.xs_passes >> XS_VEL & 1);
+    add(KC_XDEN, c.xs_passes >> XS_DEN & 1);
+    if (absorbing) add(KC_XEOS, c.xs_passes >> XS_EOS & 1);
+    return engines | staged << 8 | (c.planes & all) << 16;
+}
+
 // --- state snapshots ----------------------------------------------------------
 
 namespace {

@@ -218,13 +218,16 @@ class Simulation:
         self.plans = {}
         if tune:
             # schedules chosen by the autotuner for these transform lengths, if cached
-            from .autotune import lookup
+            from .autotune import AXIS_CLASSES, lookup
             for axis, (rad, tile) in lookup(sc.grid).items():
                 try:
                     self._plan(self.lib.kw_suggest_plan, axis, rad, tile)
                     self.plans[axis] = (rad, tile)
                 except A.KwError:
                     pass
+            # (of these, the schedules that a pass of a step runs on)
+            engines = self.routes()["engines"]
+            self.plans = {a: p for a, p in self.plans.items() if engines & set(AXIS_CLASSES[a])}
 
     # ------------------------------------------------------------------
     def step(self, n: int = 1):
@@ -299,6 +302,16 @@ class Simulation:
     def _plan(self, call, axis: int, radices, tile: int):
         arr = (C.c_int32 * len(radices))(*radices) if radices else None
         A.check(call(self.handle, axis, arr, len(radices) if radices else 0, tile))
+
+    def routes(self) -> dict:
+        """Kernel classes of a step that run on the FFT engines and on staged transforms,
+        and the x passes among these that take the y transforms around them in."""
+        bits = self.lib.kw_routes(self.handle)
+
+        def pick(first, names):
+            return {c for i, c in enumerate(names) if bits >> (first + i) & 1}
+        return dict(engines=pick(0, A.KERNEL_CLASSES), staged=pick(8, A.KERNEL_CLASSES),
+                    planes=pick(16, A.KERNEL_CLASSES[5:]))
 
     def stats(self) -> dict:
         st = A.KwStats()

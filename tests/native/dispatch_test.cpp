@@ -61,9 +61,9 @@ int main(int argc, char **argv) {
     const LaunchCfg &c = s->cfg;
     const int nz = g.nz;
     std::printf("zs=%d zs_skip=%u ys=%d xs=%d xs_passes=%u planes=%u xs_adj=%u eng_x=%d eng_y=%d eng_z=%d "
-                "tb_x=%d tb_y=%d tb_z=%d lds_grad=%zu lds_div=%zu lds_absm=%zu\n",
-                c.zs, c.zs_skip, c.ys, c.xs, c.xs_passes, c.planes, c.xs_adj, c.eng_x, c.eng_y, c.eng_z, c.tb_x,
-                c.tb_y, c.tb_z, 8 * ((size_t)2 * nz + (size_t)(c.zs_grad3 ? 3 : 1) * nz * c.zs_tb_grad),
+                "routes=%u tb_x=%d tb_y=%d tb_z=%d lds_grad=%zu lds_div=%zu lds_absm=%zu\n",
+                c.zs, c.zs_skip, c.ys, c.xs, c.xs_passes, c.planes, c.xs_adj, c.eng_x, c.eng_y, c.eng_z, kw_routes(s),
+                c.tb_x, c.tb_y, c.tb_z, 8 * ((size_t)2 * nz + (size_t)(c.zs_grad3 ? 3 : 1) * nz * c.zs_tb_grad),
                 8 * ((size_t)2 * nz + (size_t)nz * c.zs_tb), 8 * ((size_t)2 * nz + (size_t)2 * nz * c.zs_tb_absm));
     kw_destroy(s);
     std::free(ws);

@@ -77,3 +77,23 @@ def test_a_forced_axis_leaves_the_others(route, shape, medium):
     # a refused schedule changes nothing
     got = route(shape, medium, "set:1:7,11:0")
     assert got["status"] != [0] and {k: got[k] for k in STAGED} == {k: want[k] for k in STAGED}
+
+
+YF, YI, ZG, ZD, ZA, XV, XD, XE = (1 << i for i in range(8))
+X = XV | XD | XE
+
+
+# what kw_routes says: the classes on engines, on staged transforms and on planes
+@pytest.mark.parametrize("shape,medium,plans,engines,staged,planes", [
+    ((30, 8, 6), "maps", [], 0, YF | ZG | ZD | ZA | X, 7),
+    ((30, 8, 6), "lossless", [], 0, YF | ZG | ZD | XV | XD, 3),
+    ((250, 135, 20), "maps", [], 0, 255, 0),
+    ((250, 135, 48), "maps", [], 0, 255, 1),
+    ((250, 135, 20), "lossless", [], 0, YF | YI | ZG | ZD | XV | XD, 0),
+    ((64, 64, 256), "water", [], YF | ZG | ZA, ZD | X, 7),
+    ((512, 64, 64), "water", [], YF | YI | XD | XE, ZG | ZD | ZA | XV, 1),
+    ((30, 8, 6), "maps", ["set:0::0"], X, YF | YI | ZG | ZD | ZA, 0),
+    ((250, 135, 20), "maps", ["set:2::0", "hint:1:9,15:0"], ZG | ZD | ZA, YF | YI | X, 0),
+])
+def test_routes_name_every_class_once(route, shape, medium, plans, engines, staged, planes):
+    assert route(shape, medium, *plans)["routes"] == engines | staged << 8 | planes << 16

@@ -107,3 +107,17 @@ def test_one_axis_on_the_engines(kw, shape, axis):
         sim.close()
     for staged, mixed in zip(*outs):
         _same(mixed, staged)
+
+
+# tuned schedules are known for these lengths (x 80, y 160, z 160; 64 on every axis); a plan
+# is reported only where a pass runs on it
+@pytest.mark.parametrize("shape,plans", [((160, 160, 16), set()), ((160, 160, 160), set()), ((64, 64, 32), {1}),
+                                         ((128, 64, 32), {0, 1})])
+def test_reported_plans_are_used(kw, shape, plans):
+    A, Simulation = kw
+    scen = _case(*shape, "water")
+    sim = Simulation(scen)
+    r = sim.routes()
+    assert r["engines"] | r["staged"] <= set(A.KERNEL_CLASSES) and not r["engines"] & r["staged"]
+    assert set(sim.plans) == plans
+    sim.close()
