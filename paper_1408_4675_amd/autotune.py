@@ -4,10 +4,11 @@ For each axis of a grid it times candidate radix schedules (and, for the
 column passes, column-tile widths; for the x rows, rows per block) with the
 library's per-kernel HIP-event profiling, keeps the fastest, and caches the
 choice as JSON keyed by device architecture, axis kind and transform length.
-`Simulation` applies cached choices automatically, to the passes that run on
-the radix-pass engines (the passes on staged transforms have schedules of their
-own); without a cache the library's built-in defaults are used.  This plays the role that FFT planning
-by measurement plays in the paper's cluster code (Section 3.4), but the search
+`Simulation` applies cached choices automatically: as hints, which serve the
+passes on the radix-pass engines and leave those on staged transforms (with
+schedules of their own) where they are, or, where the step was measured faster
+with the schedule than with the library's defaults, by force; without a cache
+the defaults are used.  This plays the role that FFT planning by measurement plays in the paper's cluster code (Section 3.4), but the search
 space is this library's own: radix factorisations 2/3/4/5/8/16(/32) and tile
 shapes of the LDS-staged passes.
 """
@@ -16,7 +17,7 @@ from __future__ import annotations
 import itertools
 import json
 import os
-from typing import Dict, List, Optional, Sequence, Tuple
+from typing import Dict, List, Optional, Sequence, Set, Tuple
 
 CACHE_ENV = "KW_TUNE_CACHE"
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "kw_tune.json")
@@ -131,12 +132,15 @@ def candidates(axis: int, n: int) -> List[Tuple[List[int], int]]:
     return [(s, t) for s, t in itertools.product(scheds, tiles)]
 
 
-def _time_axis(scen, axis: int, sched: List[int], tile: int, steps: int) -> Optional[float]:
+def _time_plan(scen, axis: Optional[int], sched: Optional[List[int]], tile: int, steps: int) -> Optional[Dict[str, float]]:
+    """ms a step of each kernel class, with a schedule forced on one axis (axis None:
+    the library's defaults); None for a schedule that does not fit."""
     from . import _abi as A
     from .simulation import Simulation
     try:
         sim = Simulation(scen, tune=False)
-        sim.set_plan(axis, sched, tile)
+        if axis is not None:
+            sim.set_plan(axis, sched, tile)
     except A.KwError:
         return None
     sim.step(2)
@@ -148,7 +152,43 @@ def _time_axis(scen, axis: int, sched: List[int], tile: int, steps: int) -> Opti
     st = sim.stats()["classes"]
     sim.profile(False)
     sim.close()
-    return sum(st[c]["ms"] - base[c]["ms"] for c in AXIS_CLASSES[axis]) / steps
+    return {c: (st[c]["ms"] - base[c]["ms"]) / steps for c in st}
+
+
+def _tune(scen, axes, steps: int, verbose: bool) -> Dict[int, Dict]:
+    """The cache entries of the axes: the fastest schedule of the engines, marked
+    "forced" where the whole step is faster with it than with the library's
+    defaults: the best of three timings of each in turn, by more than 2 % (the
+    first timing on an idle card was 2.5 % slow at 256^3, the next two 0.5 % apart).
+    An axis whose passes run on staged transforms by default is left there by an
+    entry without the mark."""
+    def step_ms(axis, sched, tile):
+        return sum(_time_plan(scen, axis, sched, tile, steps).values())
+
+    out = {}
+    for axis in axes:
+        n = lengths(scen.grid)[axis]
+        best = None
+        for sched, tile in candidates(axis, n):
+            ms = _time_plan(scen, axis, sched, tile, steps)
+            if ms is None:
+                continue
+            own = sum(ms[c] for c in AXIS_CLASSES[axis])
+            if verbose:
+                print("tune axis %d n=%d %-14s tile %2d: %.4f ms/step" % (axis, n, sched, tile, own),
+                      flush=True)
+            if best is None or own < best[2]:
+                best = (sched, tile, own)
+        if best is None:
+            continue
+        out[axis] = dict(radices=best[0], tile=best[1], ms=best[2])
+        pairs = [(step_ms(None, None, 0), step_ms(axis, *best[:2])) for _ in range(3)]
+        default, forced_ms = (min(p[i] for p in pairs) for i in (0, 1))
+        if forced_ms < 0.98 * default:
+            out[axis]["forced"] = True
+        if verbose:
+            print("tune axis %d: step %.4f ms with it, %.4f ms by default" % (axis, forced_ms, default), flush=True)
+    return out
 
 
 def tune(scen, axes=(0, 1, 2), steps: int = 4, verbose: bool = True, save: bool = True) -> Dict:
@@ -156,29 +196,16 @@ def tune(scen, axes=(0, 1, 2), steps: int = 4, verbose: bool = True, save: bool 
     record the fastest in the cache.  Returns {axis: (schedule, tile, ms)}."""
     cache = load_cache()
     arch = _arch()
-    result = {}
-    for axis in axes:
-        n = lengths(scen.grid)[axis]
-        best = None
-        for sched, tile in candidates(axis, n):
-            ms = _time_axis(scen, axis, sched, tile, steps)
-            if ms is None:
-                continue
-            if verbose:
-                print("tune axis %d n=%d %-14s tile %2d: %.4f ms/step" % (axis, n, sched, tile, ms),
-                      flush=True)
-            if best is None or ms < best[2]:
-                best = (sched, tile, ms)
-        if best is not None:
-            result[axis] = best
-            cache[key(axis, n, arch)] = dict(radices=best[0], tile=best[1], ms=best[2])
+    found = _tune(scen, axes, steps, verbose)
     if save:
+        for axis, e in found.items():
+            cache[key(axis, lengths(scen.grid)[axis], arch)] = e
         save_cache(cache)
-    return result
+    return {axis: (e["radices"], e["tile"], e["ms"]) for axis, e in found.items()}
 
 
-def lookup(grid) -> Dict[int, Tuple[List[int], int]]:
-    """Choices for the axes of `grid`: the user's cache first, then the table
+def _entries(grid) -> Dict[int, Dict]:
+    """Cached choices for the axes of `grid`: the user's cache first, then the table
     shipped with the package ({} when neither has an entry)."""
     arch = _arch()
     tables = (load_cache(), shipped_table(arch))
@@ -187,9 +214,20 @@ def lookup(grid) -> Dict[int, Tuple[List[int], int]]:
         for tab in tables:
             e = tab.get(key(axis, n, arch))
             if e:
-                out[axis] = (list(e["radices"]), int(e.get("tile", 0)))
+                out[axis] = e
                 break
     return out
+
+
+def lookup(grid) -> Dict[int, Tuple[List[int], int]]:
+    """{axis: (schedule, tile)} of the cached choices for `grid`."""
+    return {axis: (list(e["radices"]), int(e.get("tile", 0))) for axis, e in _entries(grid).items()}
+
+
+def forced(grid) -> Set[int]:
+    """Axes of `grid` whose cached schedule made the step faster than the library's
+    defaults did: applied with kw_set_plan, the others as hints."""
+    return {axis for axis, e in _entries(grid).items() if e.get("forced")}
 
 
 def tune_table(sizes, steps: int = 3, out: Optional[str] = None, verbose: bool = True) -> Dict:
@@ -210,10 +248,8 @@ def tune_table(sizes, steps: int = 3, out: Optional[str] = None, verbose: bool =
                 shape[axis] = n
                 jobs.append((sc.small_case(*shape, seed=0, steps=8), (axis,)))
         for scen, axes in jobs:
-            res = tune(scen, axes=axes, steps=steps, verbose=verbose, save=False)
-            for axis, (sched, tile, ms) in res.items():
-                table[key(axis, lengths(scen.grid)[axis], arch)] = dict(radices=sched, tile=tile,
-                                                                         ms=round(ms, 5))
+            for axis, e in _tune(scen, axes, steps, verbose).items():
+                table[key(axis, lengths(scen.grid)[axis], arch)] = dict(e, ms=round(e["ms"], 5))
             if verbose:
                 print("tuned n=%d axes %s" % (n, axes), flush=True)
     if out:

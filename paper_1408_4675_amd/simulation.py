@@ -218,10 +218,11 @@ class Simulation:
         self.plans = {}
         if tune:
             # schedules chosen by the autotuner for these transform lengths, if cached
-            from .autotune import AXIS_CLASSES, lookup
+            from .autotune import AXIS_CLASSES, forced, lookup
+            by_force = forced(sc.grid)
             for axis, (rad, tile) in lookup(sc.grid).items():
                 try:
-                    self._plan(self.lib.kw_suggest_plan, axis, rad, tile)
+                    self._plan(self.lib.kw_set_plan if axis in by_force else self.lib.kw_suggest_plan, axis, rad, tile)
                     self.plans[axis] = (rad, tile)
                 except A.KwError:
                     pass

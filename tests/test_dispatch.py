@@ -7,6 +7,8 @@ import subprocess
 
 import pytest
 
+from paper_1408_4675_amd import _abi as A
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1408_4675_amd", "csrc")
 NATIVE = os.path.join(ROOT, "tests", "native")
@@ -97,3 +99,27 @@ X = XV | XD | XE
 ])
 def test_routes_name_every_class_once(route, shape, medium, plans, engines, staged, planes):
     assert route(shape, medium, *plans)["routes"] == engines | staged << 8 | planes << 16
+
+
+@pytest.mark.parametrize("axis,default_ms,is_forced", [(0, 12.0, True), (0, 9.0, False), (1, 9.1, False), (2, 12.0, True)])
+def test_the_tuner_times_the_defaults_too(monkeypatch, tmp_path, axis, default_ms, is_forced):
+    """A schedule is forced only where the step with it beats the step on the library's
+    defaults; a step of the stand-in timings takes 9 ms with the best schedule."""
+    from paper_1408_4675_amd import autotune as T
+    from paper_1408_4675_amd import scenarios as sc
+    scen = sc.small_case(24, 20, 18, seed=0)
+    best = T.candidates(axis, T.lengths(scen.grid)[axis])[-1]
+
+    def timed(scen, ax, sched, tile, steps):
+        if ax is None:
+            return dict.fromkeys(A.KERNEL_CLASSES, default_ms / 8)
+        ms = dict.fromkeys(A.KERNEL_CLASSES, 9.0 / 8)
+        if (sched, tile) != best:
+            ms[T.AXIS_CLASSES[ax][0]] += 1.0
+        return ms
+    monkeypatch.setattr(T, "_time_plan", timed)
+    monkeypatch.setenv(T.CACHE_ENV, str(tmp_path / "cache.json"))
+    found = T.tune(scen, axes=(axis,), verbose=False)
+    assert found[axis][:2] == best
+    assert T.lookup(scen.grid) == {axis: best}
+    assert T.forced(scen.grid) == ({axis} if is_forced else set())

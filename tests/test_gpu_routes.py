@@ -121,3 +121,21 @@ def test_reported_plans_are_used(kw, shape, plans):
     assert r["engines"] | r["staged"] <= set(A.KERNEL_CLASSES) and not r["engines"] & r["staged"]
     assert set(sim.plans) == plans
     sim.close()
+
+
+@pytest.mark.parametrize("forced", [False, True])
+def test_a_cached_schedule_is_a_hint_unless_it_was_faster(kw, monkeypatch, tmp_path, forced):
+    """A cache entry of the y axis (length 100, the 20-wide engine) moves the y pass only
+    where the tuner marked it."""
+    import json
+    from paper_1408_4675_amd import autotune as T
+    A, Simulation = kw
+    path = tmp_path / "cache.json"
+    entry = dict(radices=[10, 10], tile=0, ms=1.0, **(dict(forced=True) if forced else {}))
+    path.write_text(json.dumps({T.key(1, 100): entry}))
+    monkeypatch.setenv(T.CACHE_ENV, str(path))
+    sim = Simulation(_case(40, 100, 12, "maps"))
+    sim.step(1)
+    assert ("ypass_fwd" in sim.routes()["engines"]) == forced
+    assert sim.plans == ({1: ([10, 10], 0)} if forced else {})
+    sim.close()
