@@ -356,16 +356,17 @@ void pick_zstaged(const GridDev &g, double kx_max, double ky_max, double kz_max,
     // columns a tile: 16 (a 128-byte line) while two blocks fit a CU; 8 where
     // 16 would leave the chip short of blocks
     auto lds = [&](int tb, int tiles) { return 8 * ((size_t)2 * n + (size_t)tiles * n * tb); };
+    const size_t most = std::min<size_t>(80 * 1024, max_lds);
     auto tile = [&](int tiles, int outs) {
         int tb = 16;
-        while (tb > 1 && lds(tb, tiles) > 80 * 1024) tb /= 2;
+        while (tb > 1 && lds(tb, tiles) > most) tb /= 2;
         while (tb > 8 && ((g.M + tb - 1) / tb) * g.ny * outs < 1024) tb /= 2;
         return tb;
     };
     c.zs_tb = tile(1, 2);
     c.zs_tb_absm = tile(2, 1);
     c.zs_tb_grad = tile(3, 1);
-    c.zs_grad3 = c.zs_tb_grad >= 8;
+    c.zs_grad3 = c.zs_tb_grad >= 8 && lds(c.zs_tb_grad, 3) <= max_lds;
     if (!c.zs_grad3) c.zs_tb_grad = c.zs_tb;
     if (lds(c.zs_tb, 1) > max_lds || lds(c.zs_tb_absm, 2) > max_lds) return;
     c.zs_threads = stage_threads(c.zs_axis, c.zs_tb);
@@ -381,7 +382,7 @@ void pick_ystaged(const GridDev &g, int eng0, size_t max_lds, LaunchCfg &c) {
     if (eng_fixed(eng0) || !stage_axis(n, ST_COLUMN, false, c.ys_axis)) return;
     auto lds = [&](int tb) { return 8 * ((size_t)n + (size_t)n * tb); };
     int tb = 16;
-    while (tb > 1 && lds(tb) > 80 * 1024) tb /= 2;
+    while (tb > 1 && lds(tb) > std::min<size_t>(80 * 1024, max_lds)) tb /= 2;
     while (tb > 8 && ((g.M + tb - 1) / tb) * g.nz < 512) tb /= 2;
     if (lds(tb) > max_lds) return;
     c.ys_tb = tb;

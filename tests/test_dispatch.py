@@ -123,3 +123,16 @@ def test_the_tuner_times_the_defaults_too(monkeypatch, tmp_path, axis, default_m
     assert found[axis][:2] == best
     assert T.lookup(scen.grid) == {axis: best}
     assert T.forced(scen.grid) == ({axis} if is_forced else set())
+
+
+@pytest.mark.parametrize("limit", [48 * 1024, 64 * 1024, 160 * 1024])
+@pytest.mark.parametrize("nz", [18, 64, 81, 128, 160, 192, 225, 256, 375, 486, 512, 900])
+def test_z_tiles_fit_the_lds_of_a_block(route, nz, limit):
+    """Every launch of the staged z pass: the gradient's three tiles too."""
+    for medium in ("maps", "water"):
+        got = route((40 if nz < 300 else 8, 6, nz), medium, "lds=%d" % limit)
+        if got["status"] != [0] or not got["zs"]:
+            continue                                          # refused, or on the engines
+        assert max(got["lds_grad"], got["lds_div"], got["lds_absm"]) <= limit
+    if limit == 64 * 1024:
+        assert got["zs"]
