@@ -506,8 +506,8 @@ struct Layout {
     size_t counters, drive;
     size_t tw_x, tw_post, tw_y, tw_z, kx, ky, kz, dpx, dmx, dpy, dmy, dpz, dmz;
     size_t pml[6];
-    size_t src_row, src_x, src_e, src_c, src_ac, src_as, src_sig;
-    size_t sen_row, sen_x, sen_id, sen_idx, p_max, p_sum2, series, p_min, harm, hw, useries;
+    size_t src_row, src_pos, src_e, src_c, src_ac, src_as, src_sig;
+    size_t sen_row, sen_id, sen_idx, p_max, p_sum2, series, p_min, harm, hw, useries;
     size_t med[8];             // dtr x, y, z, rho0, c0sq, nl, ta, tb
     size_t u[3], rho[3], rho_total;
     size_t S[7];
@@ -571,7 +571,7 @@ Layout make_layout(const kw_grid *g, const kw_medium *m, const Counts &c) {
     L.pml[5] = cv.take(nz * sizeof(float));
     if (c.n_src > 0) {
         L.src_row = cv.take((rows + 1) * sizeof(int));
-        L.src_x = cv.take(c.n_src * sizeof(int));
+        L.src_pos = cv.take(c.n_src * sizeof(int));
         L.src_e = cv.take(c.n_src * sizeof(int));
         L.src_c = cv.take(c.n_src * sizeof(float));
         L.src_ac = cv.take(c.n_elem * sizeof(double));
@@ -581,7 +581,6 @@ Layout make_layout(const kw_grid *g, const kw_medium *m, const Counts &c) {
     const size_t nrec = c.sen_all ? N : (size_t)c.n_sen;
     if (!c.sen_all && c.n_sen > 0) {
         L.sen_row = cv.take((rows + 1) * sizeof(int));
-        L.sen_x = cv.take(c.n_sen * sizeof(int));
         L.sen_id = cv.take(c.n_sen * sizeof(int));
         L.sen_idx = cv.take(c.n_sen * sizeof(int));
     }
@@ -1302,12 +1301,12 @@ int prepare(const kw_grid *grid, const kw_medium *medium, const kw_source *sourc
     if (cnt.n_src > 0) {
         const long ns = cnt.n_src;
         const int rows = ny * nz;
-        std::vector<int> rp(rows + 1, 0), xp(ns), el(ns);
+        std::vector<int> rp(rows + 1, 0), pos(ns), el(ns);
         std::vector<float> cf(ns);
         for (long i = 0; i < ns; ++i) {
             const long idx = source->index[i];
             rp[idx / nx + 1]++;
-            xp[i] = (int)(idx % nx);
+            pos[i] = (int)idx;
             el[i] = source->element ? source->element[i] : 0;
             // mass: dt M_xi per unit drive; force: dt; pressure: the drive itself
             cf[i] = source->kind == KW_SOURCE_MASS
@@ -1321,7 +1320,7 @@ int prepare(const kw_grid *grid, const kw_medium *medium, const kw_source *sourc
             as[e] = (double)source->amp[e] * std::sin((double)source->phase[e]);
         }
         put(L.src_row, rp.data(), rp.size() * sizeof(int));
-        put(L.src_x, xp.data(), ns * sizeof(int));
+        put(L.src_pos, pos.data(), ns * sizeof(int));
         put(L.src_e, el.data(), ns * sizeof(int));
         put(L.src_c, cf.data(), ns * sizeof(float));
         put(L.src_ac, ac.data(), ac.size() * sizeof(double));
@@ -1351,17 +1350,15 @@ int prepare(const kw_grid *grid, const kw_medium *medium, const kw_source *sourc
     if (!cnt.sen_all && cnt.n_sen > 0) {
         const long nsn = cnt.n_sen;
         const int rows = ny * nz;
-        std::vector<int> rp(rows + 1, 0), xp(nsn), id(nsn), ix(nsn);
+        std::vector<int> rp(rows + 1, 0), id(nsn), ix(nsn);
         for (long i = 0; i < nsn; ++i) {
             const long idx = sensor->index[i];
             rp[idx / nx + 1]++;
-            xp[i] = (int)(idx % nx);
             id[i] = (int)i;
             ix[i] = (int)idx;
         }
         for (int r = 0; r < rows; ++r) rp[r + 1] += rp[r];
         put(L.sen_row, rp.data(), rp.size() * sizeof(int));
-        put(L.sen_x, xp.data(), nsn * sizeof(int));
         put(L.sen_id, id.data(), nsn * sizeof(int));
         put(L.sen_idx, ix.data(), nsn * sizeof(int));
         se.n_points = (int)nsn;
@@ -1390,7 +1387,7 @@ void bind(kw_sim *s, const MediumShape &ms) {
     sd.drive = s->at<float>(L.drive);
     if (cnt.n_src > 0) {
         sd.row_ptr = s->at<int>(L.src_row);
-        sd.xpos = s->at<int>(L.src_x);
+        sd.pos = s->at<int>(L.src_pos);
         sd.elem = s->at<int>(L.src_e);
         sd.coef = s->at<float>(L.src_c);
         sd.amp_cos = s->at<double>(L.src_ac);
@@ -1400,7 +1397,7 @@ void bind(kw_sim *s, const MediumShape &ms) {
     SensorDev &se = s->sen;
     if (!cnt.sen_all && cnt.n_sen > 0) {
         se.row_ptr = s->at<int>(L.sen_row);
-        se.xpos = s->at<int>(L.sen_x);
+        se.pos = s->at<int>(L.sen_idx);
         se.sid = s->at<int>(L.sen_id);
     }
     if (L.p_max) se.p_max = s->at<float>(L.p_max);

@@ -206,7 +206,7 @@ __global__ void __launch_bounds__(512) kw_adjx_den(XArgs a, AdjDev ad, const flo
     if (any_src) {
         for (int x = t; x < nx; x += L) smap[x] = -1;
         __syncthreads();
-        for (int e = beg + t; e < end; e += L) smap[a.src.xpos[e]] = e;
+        for (int e = beg + t; e < end; e += L) smap[a.src.pos[e] - rr * nx] = e;
         __syncthreads();
     }
     const float qy = a.t.pml_y[iy], qz = a.t.pml_z[iz];

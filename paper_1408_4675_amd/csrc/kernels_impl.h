@@ -801,7 +801,7 @@ __device__ __forceinline__ bool scatter_source(const XArgs &a, float *line, int 
         for (int x = t; x < nx; x += L) mine[x] = fill;
     __syncthreads();
     for (int e = beg + t; e < end; e += L)
-        mine[a.src.xpos[e]] = a.src.coef[e] * a.src.drive[a.src.elem[e]];
+        mine[a.src.pos[e] - row * nx] = a.src.coef[e] * a.src.drive[a.src.elem[e]];
     __syncthreads();
     return true;
 }
@@ -918,7 +918,7 @@ __global__ void __launch_bounds__(512) kw_xvel(XArgs a) {
                 __syncthreads();
                 for (int e = beg + t; e < end; e += L)
                     a.sen.u_series[((size_t)slot * 3 + xi) * a.sen.n_points + a.sen.sid[e]] =
-                        mine[a.sen.xpos[e]];
+                        mine[a.sen.pos[e] - rr * nx];
                 __syncthreads();
             }
         }
@@ -955,7 +955,7 @@ __device__ __forceinline__ void record_mask(const XArgs &a, float *line, int row
     const int slot = step - a.sen.record_start;
     for (int e = beg + t; e < end; e += L) {
         const int id = a.sen.sid[e];
-        const float pv = mine[a.sen.xpos[e]];
+        const float pv = mine[a.sen.pos[e] - row * nx];
         if (a.sen.p_max) a.sen.p_max[id] = fmaxf(a.sen.p_max[id], pv);
         if (a.sen.p_min) a.sen.p_min[id] = fminf(a.sen.p_min[id], pv);
         if (a.sen.p_sum2) a.sen.p_sum2[id] += pv * pv;

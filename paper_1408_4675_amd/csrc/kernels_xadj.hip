@@ -129,7 +129,7 @@ __device__ __forceinline__ float2 source_terms(const XArgs &x, const AdjDev &ad,
     const float2 Rv = c_add(ld2(rb, i), base), d = x.m.nonlinear ? ld2(dfw, i) : make_float2(0.0f, 0.0f);
     float2 t = make_float2(0.0f, 0.0f);
     for (int e = src.row_ptr[row]; e < src.row_ptr[row + 1]; ++e) {
-        const int o = src.xpos[e] - xp;
+        const int o = src.pos[e] - row * x.g.nx - xp;
         if (o != 0 && o != 1) continue;
         const float R = o ? Rv.y : Rv.x, den = 1.0f + 2.0f * dt * (o ? d.y : d.x);
         ad.rsrc[(size_t)g * ad.n_src + e] = R;
@@ -150,9 +150,12 @@ __global__ void KW_XS_BOUNDS(512, 3) kw_adjx_den_s(XSArgs a, AdjDev ad, const fl
     if (any_src) {
         for (int i = threadIdx.x; i < P.rows * words; i += blockDim.x) mask[i] = 0;
         __syncthreads();
-        for_points(src.row_ptr, row0, P.rows, [&](int e, int row) __attribute__((always_inline)) {
-            const int xp = src.xpos[e];
-            atomicOr(mask + (row - row0) * words + xp / 32, 1u << (xp % 32));
+        for_points(src.row_ptr, row0, P.rows, [&](const int (&e)[kPoints], const bool (&ok)[kPoints]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < kPoints; ++k) {
+                const int i = src.pos[e[k]] - row0 * x.g.nx, row = i / x.g.nx, xp = i - row * x.g.nx;
+                if (ok[k]) atomicOr(mask + row * words + xp / 32, 1u << (xp % 32));
+            }
         });
     }
     if constexpr (ABS) {

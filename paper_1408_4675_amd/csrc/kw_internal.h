@@ -74,7 +74,7 @@ struct Tables {
 struct SourceDev {
     int n_elements;
     const int *row_ptr;      // [rows + 1] CSR over grid rows (null -> no source)
-    const int *xpos;         // x of each source point
+    const int *pos;          // grid point of each source point
     const int *elem;         // element of each point
     const float *coef;       // 2 dt / (3 c0 dx) at each point
     const double *amp_cos;   // a_e cos(phi_e)
@@ -92,7 +92,7 @@ struct SensorDev {
     int all_points;          // 1 -> one accumulator per grid point
     int n_points;
     const int *row_ptr;      // [rows + 1] CSR (mask mode)
-    const int *xpos;
+    const int *pos;
     const int *sid;          // sensor id (position in the sorted index list)
     float *p_max;            // null when not recorded
     float *p_sum2;           // null when neither p_rms nor intensity is recorded

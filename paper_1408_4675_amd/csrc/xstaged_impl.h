@@ -395,15 +395,66 @@ __device__ __forceinline__ Rows rows_begin(const XSArgs &a, float2 *lds, const f
     return P;          // (the first barrier is that of to_points)
 }
 
-// f(e, row) for the entries of the CSR list over the block's rows; a wavefront
-// takes a row
+// f(e, ok) over the entries of the CSR list of the block's rows, kPoints to a thread and
+// round: entries e[k], those without ok[k] a repeated one that is not to be stored.  The
+// entries of neighbouring rows follow each other and name their grid point, so the threads
+// share them out whatever the rows hold, and a round's loads are in flight together: a
+// plane's points may all be the work of one block, which waits for memory at each step.
+// us of the pressure pass, a wavefront a row and one point a lane, and now (beside them
+// the engine and its y pass, which spread a plane's points over many blocks): 42 sensors
+// in one plane of 64^3 21.5 -> 15.4 (18), at all of its points 25.1 -> 20.4 (20), of 16 x
+// 256 57 -> 22 (39); velocity with force sources at half the points of a plane of 16 x 256
+// 41 -> 20 (40)
+constexpr int kPoints = 4;
 template <class F>
 __device__ __forceinline__ void for_points(const int *row_ptr, int row0, int ny, F f) {
-    const int wave = threadIdx.x / warpSize, lane = threadIdx.x % warpSize;
-    for (int y = wave; y < ny; y += blockDim.x / warpSize) {
-        const int end = row_ptr[row0 + y + 1];
-        for (int e = row_ptr[row0 + y] + lane; e < end; e += warpSize) f(e, row0 + y);
+    const int end = row_ptr[row0 + ny];
+    for (int e0 = row_ptr[row0] + threadIdx.x; e0 < end; e0 += kPoints * blockDim.x) {
+        int e[kPoints];
+        bool ok[kPoints];
+#pragma unroll
+        for (int k = 0; k < kPoints; ++k) {
+            const int i = e0 + k * (int)blockDim.x;
+            ok[k] = i < end;
+            e[k] = ok[k] ? i : e0;
+        }
+        f(e, ok);
     }
+}
+// a source's values at a round's entries, and where
+__device__ __forceinline__ void source_values(const SourceDev &src, const int (&e)[kPoints], int (&at)[kPoints],
+                                              float (&v)[kPoints]) {
+    int el[kPoints];
+#pragma unroll
+    for (int k = 0; k < kPoints; ++k) {
+        at[k] = src.pos[e[k]];
+        el[k] = src.elem[e[k]];
+        v[k] = src.coef[e[k]];
+    }
+#pragma unroll
+    for (int k = 0; k < kPoints; ++k) v[k] *= src.drive[el[k]];
+}
+// the values of f at a round's entries of the sensor, and their slots
+__device__ __forceinline__ void sensor_values(const SensorDev &s, const float *f, const int (&e)[kPoints],
+                                              int (&id)[kPoints], float (&v)[kPoints]) {
+    int at[kPoints];
+#pragma unroll
+    for (int k = 0; k < kPoints; ++k) {
+        at[k] = s.pos[e[k]];
+        id[k] = s.sid[e[k]];
+    }
+#pragma unroll
+    for (int k = 0; k < kPoints; ++k) v[k] = f[at[k]];
+}
+// dst[i] = f(dst[i], k) for the entries that count
+template <class T, class F>
+__device__ __forceinline__ void update_points(T *dst, const int (&id)[kPoints], const bool (&ok)[kPoints], F f) {
+    T o[kPoints];
+#pragma unroll
+    for (int k = 0; k < kPoints; ++k) o[k] = dst[id[k]];
+#pragma unroll
+    for (int k = 0; k < kPoints; ++k)
+        if (ok[k]) dst[id[k]] = f(o[k], k);
 }
 __device__ __forceinline__ bool rows_have_points(const int *row_ptr, int row0, int ny) {
     return row_ptr && row_ptr[row0 + ny] > row_ptr[row0];
@@ -461,34 +512,54 @@ struct AllPoints {
     }
 };
 
-// pressure sources and mask sensors of the block's rows, on a pressure written to p
-__device__ __forceinline__ void pressure_points(const XSArgs &a, const Rows &P, float *p,
+// What a block's rows hold of pressure sources and mask sensors (block-uniform).  Both
+// work on a pressure in memory; only a source changes it, so that its forward transform
+// waits for a second sweep.  (A second sweep for sensors too, and a wavefront a row in
+// for_points: 64^3 water with point sources and sensors 93 us a step, engines 90, now 76)
+struct PressurePoints {
+    bool source, any;
+    __device__ __forceinline__ PressurePoints(const XArgs &x, int row0, int ny)
+        : source(x.src.kind == KW_SOURCE_PRESSURE && rows_have_points(x.src.row_ptr, row0, ny)),
+          any(source || (!x.sen.all_points && rows_have_points(x.sen.row_ptr, row0, ny))) {}
+};
+// the sources and sensors, on a pressure written to p
+__device__ __forceinline__ void pressure_points(const XSArgs &a, const Rows &P, const PressurePoints &pts, float *p,
                                                       int row0, int step, bool rec) {
     const XArgs &x = a.x;
-    const int nx = x.g.nx, ny = P.rows;
+    const int ny = P.rows;
     __syncthreads();
-    if (x.src.kind == KW_SOURCE_PRESSURE && rows_have_points(x.src.row_ptr, row0, ny)) {
-        for_points(x.src.row_ptr, row0, ny, [&](int e, int row) __attribute__((always_inline)) {
+    if (pts.source) {
+        for_points(x.src.row_ptr, row0, ny, [&](const int (&e)[kPoints], const bool (&ok)[kPoints]) __attribute__((always_inline)) {
+            int at[kPoints];
+            float v[kPoints];
+            source_values(x.src, e, at, v);
             // (a drive of NaN leaves the pressure as it is, as in finish_pressure)
-            const float v = x.src.coef[e] * x.src.drive[x.src.elem[e]];
-            if (v == v) p[(size_t)row * nx + x.src.xpos[e]] = v;
+#pragma unroll
+            for (int k = 0; k < kPoints; ++k)
+                if (ok[k] && v[k] == v[k]) p[at[k]] = v[k];
         });
         __syncthreads();
     }
     const SensorDev &s = x.sen;
     if (rec && !s.all_points && rows_have_points(s.row_ptr, row0, ny)) {
         const int slot = step - s.record_start;
-        for_points(s.row_ptr, row0, ny, [&](int e, int row) __attribute__((always_inline)) {
-            const int id = s.sid[e];
-            const float pv = p[(size_t)row * nx + s.xpos[e]];
-            if (s.p_max) s.p_max[id] = fmaxf(s.p_max[id], pv);
-            if (s.p_min) s.p_min[id] = fminf(s.p_min[id], pv);
-            if (s.p_sum2) s.p_sum2[id] += pv * pv;
-            if (s.series && slot < s.capacity) s.series[(size_t)slot * s.n_points + id] = pv;
+        for_points(s.row_ptr, row0, ny, [&](const int (&e)[kPoints], const bool (&ok)[kPoints]) __attribute__((always_inline)) {
+            int id[kPoints];
+            float pv[kPoints];
+            sensor_values(s, p, e, id, pv);
+            if (s.series && slot < s.capacity) {
+                float *const row = s.series + (size_t)slot * s.n_points;
+#pragma unroll
+                for (int k = 0; k < kPoints; ++k)
+                    if (ok[k]) row[id[k]] = pv[k];
+            }
+            if (s.p_max) update_points(s.p_max, id, ok, [&](float o, int k) { return fmaxf(o, pv[k]); });
+            if (s.p_min) update_points(s.p_min, id, ok, [&](float o, int k) { return fminf(o, pv[k]); });
+            if (s.p_sum2) update_points(s.p_sum2, id, ok, [&](float o, int k) { return o + pv[k] * pv[k]; });
             for (int h = 0; h < s.n_harm; ++h) {
-                float2 *acc = reinterpret_cast<float2 *>(s.harm) + (size_t)h * s.n_points + id;
                 const float c = s.hw[2 * h], sn = s.hw[2 * h + 1];
-                *acc = make_float2(acc->x + pv * c, acc->y - pv * sn);
+                update_points(reinterpret_cast<float2 *>(s.harm) + (size_t)h * s.n_points, id, ok,
+                              [&](float2 o, int k) { return make_float2(o.x + pv[k] * c, o.y - pv[k] * sn); });
             }
         });
     }
@@ -565,7 +636,7 @@ __device__ __forceinline__ void to_spectra(const XSArgs &a, const Rows &P, int n
 
 // Eq. (4b), u <- q (q u - dt/rho0 dp); blockIdx.y: the velocity component.
 // POINTS: force sources or a velocity series, handled on the stored u between
-// the two transforms
+// the two transforms (the second, from u, only in blocks with force points)
 KW_XS_TEMPLATE, bool POINTS>
 __global__ void KW_XS_BOUNDS(1024, 4) kw_xvel_s(XSArgs a) {
     KW_XS_BEGIN(pml_sy, pml_sz)
@@ -574,6 +645,8 @@ __global__ void KW_XS_BOUNDS(1024, 4) kw_xvel_s(XSArgs a) {
     float *const u = pick3(x.fld, xi);
     const Coef dtr = xi == 0 ? x.m.dtr[0] : xi == 1 ? x.m.dtr[1] : x.m.dtr[2];
     const float *const q_rows = xi == 1 ? P.qy : P.qz;
+    const bool force = POINTS && x.src.kind == KW_SOURCE_FORCE && xi == x.src.axis &&
+                       rows_have_points(x.src.row_ptr, row0, P.rows);        // block-uniform
     x_middle<RSM>(a, P, roff, [&](auto RC, const XTask &T, int off, int j) __attribute__((always_inline)) {
         constexpr int R = decltype(RC)::value;
         float2 u0[R], d[R], v[R];
@@ -589,29 +662,38 @@ __global__ void KW_XS_BOUNDS(1024, 4) kw_xvel_s(XSArgs a) {
             v[r].y = q.y * (q.y * u0[r].y - d[r].y * v[r].y);
         }
         st_run<R>(u, T, v);
-        if constexpr (!POINTS) run_forward<R>(P, P.sh + off, j, v);
+        if (!force) run_forward<R>(P, P.sh + off, j, v);
     });
     if constexpr (POINTS) {
-        const int nx = x.g.nx;
-        if (x.src.kind == KW_SOURCE_FORCE && xi == x.src.axis && rows_have_points(x.src.row_ptr, row0, P.rows)) {
-            for_points(x.src.row_ptr, row0, P.rows, [&](int e, int row) __attribute__((always_inline)) {
-                u[(size_t)row * nx + x.src.xpos[e]] += x.src.coef[e] * x.src.drive[x.src.elem[e]];
+        if (force) {
+            for_points(x.src.row_ptr, row0, P.rows, [&](const int (&e)[kPoints], const bool (&ok)[kPoints]) __attribute__((always_inline)) {
+                int at[kPoints];
+                float v[kPoints];
+                source_values(x.src, e, at, v);
+                update_points(u, at, ok, [&](float o, int k) { return o + v[k]; });
             });
             __syncthreads();
         }
         // u^(n+1/2) is recorded with p^(n+1): step counter n + 1, already advanced
         const int step = *x.cnt.step, slot = step - x.sen.record_start;
         if (x.sen.u_series && step >= x.sen.record_start && slot < x.sen.capacity)
-            for_points(x.sen.row_ptr, row0, P.rows, [&](int e, int row) __attribute__((always_inline)) {
-                x.sen.u_series[((size_t)slot * 3 + xi) * x.sen.n_points + x.sen.sid[e]] =
-                    u[(size_t)row * nx + x.sen.xpos[e]];
+            for_points(x.sen.row_ptr, row0, P.rows, [&](const int (&e)[kPoints], const bool (&ok)[kPoints]) __attribute__((always_inline)) {
+                int id[kPoints];
+                float v[kPoints];
+                sensor_values(x.sen, u, e, id, v);
+                float *const series = x.sen.u_series + ((size_t)slot * 3 + xi) * x.sen.n_points;
+#pragma unroll
+                for (int k = 0; k < kPoints; ++k)
+                    if (ok[k]) series[id[k]] = v[k];
             });
-        x_middle<RSM>(a, P, roff, [&](auto RC, const XTask &T, int off, int j) __attribute__((always_inline)) {
-            constexpr int R = decltype(RC)::value;
-            float2 v[R];
-            ld_run<R>(u, T, v);
-            run_forward<R>(P, P.sh + off, j, v);
-        });
+        if (force) {
+            x_middle<RSM>(a, P, roff, [&](auto RC, const XTask &T, int off, int j) __attribute__((always_inline)) {
+                constexpr int R = decltype(RC)::value;
+                float2 v[R];
+                ld_run<R>(u, T, v);
+                run_forward<R>(P, P.sh + off, j, v);
+            });
+        }
     }
     to_spectra<RSY, RSM, RSP, PLANES, true, 1>(a, P, 1, [&](int) __attribute__((always_inline)) { return pick3(x.Sout, xi) + soff; });
 }
@@ -633,19 +715,20 @@ __device__ __forceinline__ void lossless_eos(const Medium &m, const XTask &T, co
 }
 
 // The sums rho of a task's points on: stored and transformed (ABS), or to the pressure,
-// whose transform starts unless point sensors or sources come first
+// which is stored for point sensors and sources and whose transform starts unless a
+// source comes first
 template <bool ABS, int R>
 __device__ __forceinline__ void den_finish(const XSArgs &a, const Rows &P, float2 *out_rho, const XTask &T,
-                                           int off, int j, int step, bool rec, bool points, float2 (&sr)[R]) {
+                                           int off, int j, int step, bool rec, const PressurePoints &pts,
+                                           float2 (&sr)[R]) {
     if constexpr (ABS) {
         st_run<R>(a.x.rho_total, T, sr);
         run_forward<R>(P, out_rho + off, j, sr);
     } else {
         float2 p[R];
         lossless_eos<R>(a.x.m, T, sr, p);
-        if (points) {
-            st_run<R>(a.scr, T, p);
-        } else {
+        if (pts.any) st_run<R>(a.scr, T, p);
+        if (!pts.source) {
             AllPoints{a, step, rec}.template run<R>(T, p);
             run_forward<R>(P, P.sh + off, j, p);
         }
@@ -664,8 +747,7 @@ __global__ void KW_XS_BOUNDS(768, 3) kw_xden_s(XSArgs a) {
     const bool src = x.src.kind == KW_SOURCE_MASS && rows_have_points(x.src.row_ptr, row0, P.rows);
     const int step = *x.cnt.step;
     const bool rec = step >= x.sen.record_start;
-    const bool points = !ABS && ((x.src.kind == KW_SOURCE_PRESSURE && rows_have_points(x.src.row_ptr, row0, P.rows)) ||
-                                 (!x.sen.all_points && rows_have_points(x.sen.row_ptr, row0, P.rows)));
+    const PressurePoints pts(x, row0, P.rows);               // (used without absorption)
     float2 *const out_rho = P.set(sumd ? 1 : 0);
     x_middle<RSM>(a, P, roff, [&](auto RC, const XTask &T, int off, int j) __attribute__((always_inline)) {
         constexpr int R = decltype(RC)::value;
@@ -713,20 +795,22 @@ __global__ void KW_XS_BOUNDS(768, 3) kw_xden_s(XSArgs a) {
                 run_forward<R>(P, P.sh + off, j, sd);
             }
         }
-        if (!src) den_finish<ABS, R>(a, P, out_rho, T, off, j, step, rec, points, sr);
+        if (!src) den_finish<ABS, R>(a, P, out_rho, T, off, j, step, rec, pts, sr);
     });
     if (src) {                                               // block-uniform
         // dt M added to each component at the source points, then rho from the
         // components
-        for_points(x.src.row_ptr, row0, P.rows, [&](int e, int row) __attribute__((always_inline)) {
-            const size_t i = (size_t)row * x.g.nx + x.src.xpos[e];
-            const float s = x.src.coef[e] * x.src.drive[x.src.elem[e]];
+        for_points(x.src.row_ptr, row0, P.rows, [&](const int (&e)[kPoints], const bool (&ok)[kPoints]) __attribute__((always_inline)) {
+            int at[kPoints];
+            float v[kPoints];
+            source_values(x.src, e, at, v);
 #pragma unroll
             for (int g = 0; g < 3; ++g) {
-                float *const rho = pick3(x.fld, g);
-                const float nw = rho[i] + s;
-                rho[i] = nw;
-                if (x.rec_d[0]) pick3(x.rec_rho, g)[i] = nw;
+                float *const rec = x.rec_d[0] ? pick3(x.rec_rho, g) : nullptr;
+                update_points(pick3(x.fld, g), at, ok, [&](float o, int k) {
+                    if (rec) rec[at[k]] = o + v[k];
+                    return o + v[k];
+                });
             }
         });
         __syncthreads();
@@ -738,7 +822,7 @@ __global__ void KW_XS_BOUNDS(768, 3) kw_xden_s(XSArgs a) {
             ld_run<R>(x.fld[2], T, w2);
 #pragma unroll
             for (int r = 0; r < R; ++r) sr[r] = c_add(c_add(sr[r], w1[r]), w2[r]);
-            den_finish<ABS, R>(a, P, out_rho, T, off, j, step, rec, points, sr);
+            den_finish<ABS, R>(a, P, out_rho, T, off, j, step, rec, pts, sr);
         });
     }
     if constexpr (ABS) {
@@ -746,8 +830,8 @@ __global__ void KW_XS_BOUNDS(768, 3) kw_xden_s(XSArgs a) {
             return (sumd && s == 0 ? x.Sout[0] : x.Sout[1]) + soff;
         });
     } else {
-        if (points) {
-            pressure_points(a, P, a.scr, row0, step, rec);
+        if (pts.any) pressure_points(a, P, pts, a.scr, row0, step, rec);
+        if (pts.source) {
             x_middle<RSM>(a, P, roff, [&](auto RC, const XTask &T, int off, int j) __attribute__((always_inline)) {
                 constexpr int R = decltype(RC)::value;
                 float2 p[R];
@@ -769,6 +853,7 @@ __global__ void KW_XS_BOUNDS(1024, 4) kw_xeos_s(XSArgs a) {
     to_points<RSY, RSM, RSP, PLANES, MERGED ? 1 : 2>(a, P, [&](int s) __attribute__((always_inline)) { return (s ? x.Sin[1] : x.Sin[0]) + soff; });
     const int step = *x.cnt.step;
     const bool rec = step >= x.sen.record_start;
+    const PressurePoints pts(x, row0, P.rows);
     x_middle<RSM>(a, P, roff, [&](auto RC, const XTask &T, int off, int j) __attribute__((always_inline)) {
         constexpr int R = decltype(RC)::value;
         float2 p[R], v[R], c[MERGED ? 1 : R];
@@ -793,22 +878,23 @@ __global__ void KW_XS_BOUNDS(1024, 4) kw_xeos_s(XSArgs a) {
                 p[r].y += c[r].y * v[r].y;
             }
         }
-        if constexpr (POINTS) {
-            st_run<R>(a.scr, T, p);
-        } else {
+        if (POINTS && pts.any) st_run<R>(a.scr, T, p);
+        if (!POINTS || !pts.source) {
             AllPoints{a, step, rec}.template run<R>(T, p);
             run_forward<R>(P, P.sh + off, j, p);
         }
     });
     if constexpr (POINTS) {
-        pressure_points(a, P, a.scr, row0, step, rec);
-        x_middle<RSM>(a, P, roff, [&](auto RC, const XTask &T, int off, int j) __attribute__((always_inline)) {
-            constexpr int R = decltype(RC)::value;
-            float2 p[R];
-            ld_run<R>(a.scr, T, p);
-            AllPoints{a, step, rec}.template run<R>(T, p);
-            run_forward<R>(P, P.sh + off, j, p);
-        });
+        if (pts.any) pressure_points(a, P, pts, a.scr, row0, step, rec);
+        if (pts.source) {
+            x_middle<RSM>(a, P, roff, [&](auto RC, const XTask &T, int off, int j) __attribute__((always_inline)) {
+                constexpr int R = decltype(RC)::value;
+                float2 p[R];
+                ld_run<R>(a.scr, T, p);
+                AllPoints{a, step, rec}.template run<R>(T, p);
+                run_forward<R>(P, P.sh + off, j, p);
+            });
+        }
     }
     to_spectra<RSY, RSM, RSP, PLANES, false, 1>(a, P, 1, [&](int) __attribute__((always_inline)) { return x.Sout[0] + soff; });
 }

@@ -8,7 +8,9 @@ import dataclasses
 import numpy as np
 import pytest
 
+from oracle import Oracle
 from paper_1408_4675_amd import scenarios as sc
+from tests._parity import compare_outputs
 
 pytestmark = pytest.mark.gpu
 
@@ -139,3 +141,35 @@ def test_a_cached_schedule_is_a_hint_unless_it_was_faster(kw, monkeypatch, tmp_p
     assert ("ypass_fwd" in sim.routes()["engines"]) == forced
     assert sim.plans == ({1: ([10, 10], 0)} if forced else {})
     sim.close()
+
+
+# planes of 64 x 64 (all three passes; two rounds of points a block), of 96 x 72 (velocity),
+# rows of a generic length
+@pytest.mark.parametrize("shape", [(64, 64, 6), (96, 72, 48), (100, 90, 4)])
+@pytest.mark.parametrize("kind,axis", [(sc.SOURCE_MASS, 0), (sc.SOURCE_FORCE, 1), (sc.SOURCE_PRESSURE, 0)])
+@pytest.mark.parametrize("medium", ["maps", "lossless"])
+def test_points_that_fill_a_plane(kw, shape, kind, axis, medium):
+    """Sources at every point of a z plane but some rows, sensors at every point of the next
+    plane and at one point of the last: every accumulator and series of these."""
+    A, Simulation = kw
+    nx, ny, nz = shape
+    scen = _case(nx, ny, nz, medium, mask=True)
+    plane = np.arange(nx * ny, dtype=np.int64)
+    src = plane[(plane // nx % 5 != 2) & (plane % nx != 1)] + nx * ny
+    sen = np.concatenate([plane + 2 * nx * ny, [nx * ny * nz - 7]])
+    rec = (sc.REC_P_MAX | sc.REC_P_MIN | sc.REC_P_RMS | sc.REC_P_SERIES | sc.REC_U_SERIES |
+           sc.REC_HARMONICS | sc.REC_P_FINAL | sc.REC_U_FINAL)
+    n = 3
+    source = sc.Source(index=src, amp=np.array([1e5, 2e5, 3e5], np.float32), phase=np.array([0.3, 1.1, 2.0], np.float32),
+                       element=(np.arange(src.size) % n).astype(np.int32), kind=kind, axis=axis)
+    scen = scen.replace(source=source, sensor=dataclasses.replace(scen.sensor, record=rec, index=sen,
+                                                                  series_capacity=STEPS, n_harmonics=2))
+    print("\n[case] %s kind %d" % (scen.name, kind), flush=True)
+    sim = Simulation(scen, tune=False)
+    sim.step(STEPS)
+    orc = Oracle(scen)
+    orc.step(STEPS)
+    errs, _ = compare_outputs(sim, orc, scen, [])
+    sim.close()
+    for k, e in errs.items():
+        assert e <= TOL, (k, e)
