@@ -378,7 +378,7 @@ void pick_zstaged(const GridDev &g, double kx_max, double ky_max, double kz_max,
 // kernels measured equal or faster on theirs)
 void pick_ystaged(const GridDev &g, int eng0, size_t max_lds, LaunchCfg &c) {
     const int n = g.ny;
-    c.ys = 0;
+    c.ys = false;
     if (eng_fixed(eng0) || !stage_axis(n, ST_COLUMN, false, c.ys_axis)) return;
     auto lds = [&](int tb) { return 8 * ((size_t)n + (size_t)n * tb); };
     int tb = 16;
@@ -387,7 +387,7 @@ void pick_ystaged(const GridDev &g, int eng0, size_t max_lds, LaunchCfg &c) {
     if (lds(tb) > max_lds) return;
     c.ys_tb = tb;
     c.ys_threads = stage_threads(c.ys_axis, tb);
-    c.ys = 2;
+    c.ys = true;
 }
 
 // Which x passes of a step run on staged transforms, which of them on z planes, and
@@ -1077,7 +1077,7 @@ int pick_tiles(kw_sim *s, int tile_y, int tile_z) {
     pick_zstaged(g, kPi / s->grid.dx, kPi / s->grid.dy, kPi / s->grid.dz, s->max_lds, c);
     if (s->engines[2]) c.zs = 0;
     pick_ystaged(g, s->eng0_y, s->max_lds, c);
-    if (s->engines[1]) c.ys = 0;
+    if (s->engines[1]) c.ys = false;
     pick_xstaged(g, s->eng0_x, s->px0, s->med.absorbing, s->merged_abs, !s->engines[1], s->max_lds, c);
     if (s->engines[0]) c.xs_passes = c.planes = c.xs_adj = 0;
     // the column passes address an element of their tile by a 32-bit byte offset

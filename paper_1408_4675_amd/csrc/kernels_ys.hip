@@ -21,9 +21,10 @@ struct YSArgs {
     ColPlan p;
 };
 
-template <RadixSet RS, bool INV>
+template <bool INV>
 __global__ void __launch_bounds__(512) kw_ystaged(YSArgs a) {
     extern __shared__ float2 lds_all[];
+    constexpr RadixSet RS = kAnyY;
     const YArgs &y = a.y;
     const ColPlan &p = a.p;
     const int ny = y.ny, M = y.M;
@@ -77,13 +78,6 @@ __global__ void __launch_bounds__(512) kw_ystaged(YSArgs a) {
     }
 }
 
-template <RadixSet RS>
-void launch_set(hipStream_t s, const LaunchCfg &c, const YSArgs &a, bool inverse, dim3 grid, size_t lds) {
-    const dim3 block(c.ys_threads);
-    if (inverse) hipLaunchKernelGGL((kw_ystaged<RS, true>), grid, block, lds, s, a);
-    else hipLaunchKernelGGL((kw_ystaged<RS, false>), grid, block, lds, s, a);
-}
-
 }  // namespace
 
 hipError_t launch_ystaged(hipStream_t s, const LaunchCfg &c, const YArgs &y, bool inverse, int nfields) {
@@ -96,8 +90,9 @@ hipError_t launch_ystaged(hipStream_t s, const LaunchCfg &c, const YArgs &y, boo
     while ((1 << a.p.ltb) < c.ys_tb) ++a.p.ltb;
     const dim3 grid(xcd_grid(a.y.ntiles * y.nz, line_group(c.ys_tb), 1), 1, nfields);
     const size_t lds = 8 * ((size_t)y.ny + (size_t)y.ny * c.ys_tb);
-    if (c.ys == 1) launch_set<kPow2Y>(s, c, a, inverse, grid, lds);
-    else launch_set<kAnyY>(s, c, a, inverse, grid, lds);
+    const dim3 block(c.ys_threads);
+    if (inverse) hipLaunchKernelGGL((kw_ystaged<true>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((kw_ystaged<false>), grid, block, lds, s, a);
     return hipGetLastError();
 }
 

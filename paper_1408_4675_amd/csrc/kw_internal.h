@@ -216,7 +216,8 @@ struct LaunchCfg {
     unsigned zs_skip;        // modes (bit ZM_*) that stay on the engines
     int zs_tb, zs_tb_grad, zs_tb_absm, zs_grad3, zs_threads;  // columns a tile; the gradient's
                              // outputs from one block; threads
-    int ys, ys_tb, ys_threads;   // y pass on staged transforms (kernels_ys.hip), as zs
+    bool ys;                 // y pass on staged transforms (kernels_ys.hip); columns a tile,
+    int ys_tb, ys_threads;   // threads
     StageAxis ys_axis;
 };
 

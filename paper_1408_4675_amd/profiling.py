@@ -72,8 +72,8 @@ def kernel_class(name: str) -> Optional[str]:
         return {"0": "zfused_grad", "1": "zfused_div", "2": "zfused_abs",
                 "3": "zfused_divt", "4": "zfused_gradt",
                 "5": "zfused_abs"}.get(m.group(1), "zfused")   # 5: merged absorption
-    # the passes on staged transforms: radix set, then direction or mode
-    m = re.search(r"kw_ystaged<\d+\w*, (true|false)>", name)
+    # the passes on staged transforms: direction, or radix set and mode
+    m = re.search(r"kw_ystaged<(true|false)>", name)
     if m:
         return "ypass_inv" if m.group(1) == "true" else "ypass_fwd"
     m = re.search(r"kw_zstaged<\d+\w*, (\d), \d>", name)

@@ -136,3 +136,15 @@ def test_z_tiles_fit_the_lds_of_a_block(route, nz, limit):
         assert max(got["lds_grad"], got["lds_div"], got["lds_absm"]) <= limit
     if limit == 64 * 1024:
         assert got["zs"]
+
+
+@pytest.mark.parametrize("name,cls", [
+    ("kw_ystaged<true>(kw::(anonymous namespace)::YSArgs)", "ypass_inv"),
+    ("kw_ystaged<false>(kw::(anonymous namespace)::YSArgs)", "ypass_fwd"),
+    ("kw_zstaged<65812ull, 0, 3>(kw::(anonymous namespace)::ZSArgs)", "zfused_grad"),
+    ("kw_zstaged<104316ull, 5, 1>(kw::(anonymous namespace)::ZSArgs)", "zfused_abs"),
+    ("kw_xden_s<104316ull, 382ull, 6012ull, false, true>(kw::(anonymous namespace)::XSArgs)", "xden"),
+])
+def test_profiled_names_of_staged_kernels(name, cls):
+    from paper_1408_4675_amd.profiling import kernel_class
+    assert kernel_class("void kw::(anonymous namespace)::" + name) == cls
