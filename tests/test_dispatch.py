@@ -29,6 +29,8 @@ def route(tmp_path_factory):
     def run(shape, medium="maps", *args):
         r = subprocess.run([exe] + [str(n) for n in shape] + [medium] + list(args),
                            stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+        if r.stdout.startswith("error="):
+            return dict(error=r.stdout)
         assert r.returncode == 0, r.stdout
         out = {}
         for word in r.stdout.split():
@@ -148,3 +150,27 @@ def test_z_tiles_fit_the_lds_of_a_block(route, nz, limit):
 def test_profiled_names_of_staged_kernels(name, cls):
     from paper_1408_4675_amd.profiling import kernel_class
     assert kernel_class("void kw::(anonymous namespace)::" + name) == cls
+
+
+def test_lengths_of_the_staged_cases(route):
+    """Which lengths of the GPU cases of the staged passes have stages: all columns but 625
+    (5^4, no three radices up to 16), all packed rows but 243, 405 and 500 (the update's
+    registers hold radices up to 8 in the first stages, 12 in the last)."""
+    from tests.test_gpu_staged import COLUMNS, ROWS
+    assert [n for n in COLUMNS if not route((8 if n > 64 else 40, 6, n))["zs"]] == [625]
+    generic = [n for n in COLUMNS if route((8, n, 5))["eng_y"] < 2]
+    assert [n for n in generic if not route((8, n, 5))["ys"]] == [625]
+    assert [m for m in ROWS if not route((2 * m, 6 if m < 200 else 5, 5))["xs_passes"]] == [243, 405, 500]
+
+
+def test_rows_without_stages(route):
+    """The packed row lengths (nx = 2 m) whose x passes run on the engines for want of stages."""
+    def smooth(n):
+        for p in (2, 3, 5):
+            while n % p == 0:
+                n //= p
+        return n == 1
+    routes = {m: route((2 * m, 5, 5)) for m in range(200, 1025) if smooth(m)}
+    assert [m for m, r in routes.items() if "error" in r] == [675, 729, 810]      # (the engines' density pass)
+    none = [m for m, r in routes.items() if "error" not in r and not r["xs_passes"]]
+    assert none == [243, 375, 405, 450, 486, 500, 540, 600, 625, 648, 720, 750, 800, 864, 900, 960, 972, 1000, 1024]

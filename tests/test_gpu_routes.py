@@ -35,6 +35,28 @@ def _case(nx, ny, nz, medium, mask=False):
                          steps=STEPS, sensor_mask=mask)
 
 
+def _check(sim, scen):
+    """A run of a simulation that has not stepped yet against the oracle."""
+    sim.step(STEPS)
+    orc = Oracle(scen)
+    orc.step(STEPS)
+    errs, _ = compare_outputs(sim, orc, scen, [])
+    sim.close()
+    for k, e in errs.items():
+        assert e <= TOL, (k, e)
+
+
+def _smooth(n):
+    while True:
+        m = n
+        for p in (2, 3, 5):
+            while m % p == 0:
+                m //= p
+        if m == 1:
+            return n
+        n += 1
+
+
 def _same(a, b):
     a, b = np.asarray(a, np.float64), np.asarray(b, np.float64)
     assert np.isfinite(a).all()
@@ -165,11 +187,74 @@ def test_points_that_fill_a_plane(kw, shape, kind, axis, medium):
     scen = scen.replace(source=source, sensor=dataclasses.replace(scen.sensor, record=rec, index=sen,
                                                                   series_capacity=STEPS, n_harmonics=2))
     print("\n[case] %s kind %d" % (scen.name, kind), flush=True)
+    _check(Simulation(scen, tune=False), scen)
+
+
+X_PASSES = {"xvel", "xden", "xeos"}
+
+
+@pytest.mark.parametrize("m", [240, 270, 320, 400, 480, 640])
+@pytest.mark.parametrize("medium", ["maps", "lossless"])
+@pytest.mark.parametrize("mask", [False, True])
+def test_long_rows(kw, m, medium, mask):
+    """x passes on rows of generic lengths up to the longest with stages, none on planes."""
+    A, Simulation = kw
+    scen = _case(2 * m, _smooth(4097 // m + 1), 4, medium, mask)
     sim = Simulation(scen, tune=False)
-    sim.step(STEPS)
-    orc = Oracle(scen)
-    orc.step(STEPS)
-    errs, _ = compare_outputs(sim, orc, scen, [])
+    print("\n[case] %s" % scen.name, flush=True)
+    r = sim.routes()
+    assert X_PASSES - (set() if medium == "maps" else {"xeos"}) <= r["staged"] and not r["planes"]
+    _check(sim, scen)
+
+
+@pytest.mark.parametrize("shape", [(640, 5, 5), (480, 6, 4), (400, 5, 5)])
+@pytest.mark.parametrize("medium", ["maps", "lossless"])
+def test_long_rows_on_planes(kw, shape, medium):
+    A, Simulation = kw
+    scen = _case(*shape, medium)
+    sim = Simulation(scen, tune=False)
+    print("\n[case] %s" % scen.name, flush=True)
+    assert sim.routes()["planes"] == X_PASSES - (set() if medium == "maps" else {"xeos"})
+    _check(sim, scen)
+
+
+@pytest.mark.parametrize("shape", [(800, 6, 8), (640, 8, 6)])
+@pytest.mark.parametrize("absorbing", [True, False])
+def test_reverse_step_on_long_rows(kw, shape, absorbing):
+    """The reverse x passes on long staged rows (800 = 2 5 8 10: 400 = 5 8 10 packed)."""
+    from oracle.adjoint import AdjointOracle
+    from paper_1408_4675_amd.adjoint import focus_gradient
+    A, Simulation = kw
+    scen = sc.small_case(*shape, seed=4, pml=2, steps=6, amp=2.0e6, n_elements=3, absorbing=absorbing)
+    scen = scen.replace(sensor=sc.Sensor(record=sc.REC_INTENSITY, record_start=3))
+    sim = Simulation(scen)
+    assert {"xvel", "xden"} <= sim.routes()["staged"]
     sim.close()
-    for k, e in errs.items():
-        assert e <= TOL, (k, e)
+    w = np.random.default_rng(6).standard_normal(scen.grid.npts)
+    ref = AdjointOracle(scen, w, workers=4)
+    ref.forward()
+    gr = ref.backward()
+    print("\n[case] %s" % scen.name, flush=True)
+    out = focus_gradient(scen, w, checkpoint_every=3)
+    e = np.linalg.norm(out["source_gradient"] - gr["dJds"]) / np.linalg.norm(gr["dJds"])
+    assert e <= TOL
+
+
+# long axes and lengths of every engine, forced to the engines (their default plans): by
+# default the staged passes take most of them
+ENGINES = [(16, 256, 8), (16, 8, 1024), (16, 1024, 8), (1024, 8, 8), (16, 8, 512), (32, 512, 6), (512, 6, 10),
+           (16, 8, 256), (24, 10, 960), (40, 6, 1024), (40, 1024, 6), (30, 8, 6), (100, 90, 4), (250, 20, 10),
+           (64, 64, 16), (96, 12, 36)]
+
+
+@pytest.mark.parametrize("shape", ENGINES)
+@pytest.mark.parametrize("medium,mask", [("maps", False), ("water", True), ("lossless", True)])
+def test_engines_against_the_oracle(kw, shape, medium, mask):
+    A, Simulation = kw
+    scen = _case(*shape, medium, mask)
+    sim = Simulation(scen, tune=False)
+    for axis in range(3):
+        sim.set_plan(axis, None)
+    print("\n[case] %s" % scen.name, flush=True)
+    assert not sim.routes()["staged"]
+    _check(sim, scen)
