@@ -265,6 +265,10 @@ bool axis_plan(int n, int axis, const std::vector<int> *rad, int &eng, FftPlan &
 // kPow2M .. kAnyP for x rows).  At least two -- one at each end of a column; the
 // update's and the real-transform split's of a row -- where the first has radix 1
 // if the length is a radix itself; the columns of a plane may have one.
+// Without stages: columns of 625 (no three radices up to 16); x rows of (packed) 243, 375,
+// 405, 450, 486, 500, 540, 600, 625, 648, 720, 750, 800, 864, 900, 960, 972, 1000, 1024
+// points, whose update would hold more than eight values a field or whose split two
+// butterflies of more than twelve: these stay on the engines.
 enum { ST_COLUMN, ST_ROW, ST_PLANE };
 bool stage_axis(int n, int kind, bool pow2, StageAxis &A) {
     // (of equals the largest last radix: an x row's update runs over M / r[0]
@@ -341,14 +345,15 @@ void pick_zstaged(const GridDev &g, double kx_max, double ky_max, double kz_max,
     c.zs = 0;
     const bool pow2 = is_pow2(n);
     if (!stage_axis(n, ST_COLUMN, pow2, c.zs_axis)) return;
-    // The fixed-width engines keep the gradient and the merged absorption of 256
-    // and 1024 points, lengths that their 16- and 32-wide threads transform in
-    // two passes (gradient at 1024: three, in 4-column tiles).  Staged against
+    // The fixed-width engines keep the gradient and the merged absorption of lengths
+    // that they transform in two passes of their full width, 16 16 and 32 32: the
+    // merged absorption runs on those two (eng_za), the gradient on the first (at 1024
+    // points on three passes in 4-column tiles, a measured exception).  Staged against
     // fixed, us a launch: gradient 256^3 77 : 74, 128 x 128 x 512 49 : 63,
     // 1024^3 10800 : 9700; merged absorption 256^3 103 : 88, 128 x 128 x 512
     // 60 : 71, 1024^3 11400 : 7800; divergence 256^3 95 : 99, 128 x 128 x 512
     // 56 : 74, 1024^3 11600 : 12500
-    c.zs_skip = n == 256 || n == 1024 ? 1u << ZM_GRAD | 1u << ZM_ABSM : 0u;
+    c.zs_skip = n == 16 * 16 || n == 32 * 32 ? 1u << ZM_GRAD | 1u << ZM_ABSM : 0u;
     // kappa as a polynomial at every wavenumber of the grid
     const double k2 = kx_max * kx_max + ky_max * ky_max + kz_max * kz_max;
     if ((double)g.half_cdt * g.half_cdt * k2 > kKappaPolyMax) return;
@@ -408,8 +413,14 @@ void pick_xstaged(const GridDev &g, int eng0, const FftPlan &plan0, bool absorbi
     const int sets[3] = {1, 3, merged ? 1 : 2};
     const int passes = absorbing ? 3 : 2;
     // Planes: the velocity pass, three blocks a plane, wherever a plane fits LDS and
-    // the blocks fill half the chip or the planes are small; the other two, one block a
-    // plane, on planes so small that launches and latency are all there is.  us, planes :
+    // there are blocks for more than half the CUs (3 48 of 256) or the planes are small; the
+    // other two, one block a plane, on planes so small that launches and latency are all
+    // there is.  us a step of water without : with velocity planes, at 24 / 32 / 48 / 64 z
+    // planes: 256 x 64 99 : 103 / 108 : 110 / 124 : 119 / 130 : 125; 1024 x 32 123 : 127 /
+    // 129 : 129 / 146 : 144 / 158 : 151; 128 x 256 135 : 133 / 134 : 133 / 157 : 148 / 167 :
+    // 155; 250 x 135 162 : 155 / 176 : 161 / 218 : 192 / 242 : 213; fields beyond the cache,
+    // 128 x 256 x 512 976 : 948, 250 x 135 x 512 1525 : 1372; least at 90 planes of one block
+    // a CU (270 blocks on 256 CUs), 160 x 160 219 : 222.  us of the pass, planes :
     // y pass, x pass, y pass: velocity 64^3 17 : 21, 96^3 28 : 41, 128^3 37 : 51, 160^3
     // 83 : 127 (rows 113), 250 x 135 x 90 92 : 122; density and
     // pressure with the y passes that they take in, 48 x 20 x 18 34 : 56, 64^3 47 : 57, but
@@ -418,9 +429,9 @@ void pick_xstaged(const GridDev &g, int eng0, const FftPlan &plan0, bool absorbi
     if (!on_planes) planes = 0;
     // Rows: the lengths of the generic engine, whose passes of a smaller radix than its
     // largest leave threads idle: us, rows : engine, velocity / density / pressure
-    // 250 x 135 x 90 (125 = 5 25) 53 : 150 / 68 : 249 / 45 : 148; 160^3 63 : 76 / 86 : 91 /
-    // 54 : 60; 360 x 270 x 120 175 : 189 / 264 : 289 / 168 : 164; 450 x 480 x 324 989 : 1061 /
-    // 1512 : 1686 / 522 : 540.  The 8- and 12-wide engines keep theirs (256^3 density
+    // 250 x 135 x 90 (125 = 5 25) 53 : 148 / 54 : 235 / 42 : 147; 160^3 63 : 75 / 71 : 88 /
+    // 53 : 58; 360 x 270 x 120 161 : 183 / 203 : 266 / 155 : 156; 450 x 480 x 324 856 : 1055 /
+    // 966 : 1550 / 496 : 536.  The 8- and 12-wide engines keep theirs (256^3 density
     // 388 : 193, 192^3 158 : 145, 96^3 32 : 28)
     const unsigned rows = eng_fixed(eng0) ? 0u : 7u;
     bool set = pow2;

@@ -4,7 +4,8 @@
 // of them: LaunchCfg::xs_adj).
 //
 // What bounds them is what bounds the forward passes, and the density pass the loads of
-// its three components one after the other (twelve wavefronts a CU; registers).  us a
+// its three components one after the other (twelve wavefronts a CU; registers: 72 bytes
+// a lane go to scratch with absorption, 20 in the equation of state).  us a
 // launch, the engines of kernels_adj.hip and these, 250 x 135 x 90: density 357 -> 143
 // (19 fields, 1.6 TB/s), equation of state 155 -> 41 (3.2 TB/s), sum 112 -> 21, velocity
 // with its y passes 245 -> 90; 128^3 velocity with its y passes 52 -> 36.

@@ -1,4 +1,4 @@
-// The staged x passes for any lengths 2^a 3^b 5^c, and the choice between them and
+// The staged x passes for the lengths 2^a 3^b 5^c that have stages, and the choice between them and
 // the kernels for powers of two (kernels_xs2.hip).
 #include "xstaged_impl.h"
 

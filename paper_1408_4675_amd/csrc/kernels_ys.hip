@@ -1,11 +1,12 @@
-// The y pass on in-place staged transforms (staged.h), any length.
+// The y pass on in-place staged transforms (staged.h), every length but 625.
 //
 // A block reads its tile's columns into the first stage's registers, exchanges
 // through LDS once (twice for three stages) and writes the last stage's results:
 // HBM traffic is the field in and out, and what bounds the pass is that copy and,
 // on small grids, the latency of the two or three phases.  Before (one butterfly
 // a thread: 135 = 3 3 15 leaves four threads of five idle in its radix-15 pass)
-// and now, us of a step's forward / inverse passes (6 / 8 fields):
+// and now, us of a step's forward / inverse passes (6 / 8 fields, none of them part of an
+// x pass):
 // 250 x 135 x 90 192 / 221 -> 73 / 85; 160^3 70 / 85 -> 54 / 68 (3.6 / 3.9 TB/s);
 // 360 x 270 x 120 480 / 557 -> 164 / 206; 450 x 480 x 324 1360 / 1851 -> 799 / 1208
 // (4.2 / 3.7 TB/s); 48 x 20 x 18 42 / 40 -> 20 / 20.

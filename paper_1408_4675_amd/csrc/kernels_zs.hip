@@ -1,5 +1,5 @@
 // The fused z pass on in-place staged transforms (staged.h): forward z FFT ->
-// k-space operator(s) -> inverse z FFT of column tiles, any length.
+// k-space operator(s) -> inverse z FFT of column tiles, every length but 625.
 //
 // A block holds a tile of tb columns in LDS.  The first stage reads global
 // memory, the last forward stage, the operator and the last inverse stage run in
@@ -12,8 +12,8 @@
 // (4 to 6 wavefronts a SIMD), then the strided 128-byte rows of a tile.  Before
 // (one-butterfly-a-thread or fixed-width engines) and now, us a launch of
 // gradient / divergence / absorption: 250 x 135 x 90 46 / 55 / 40 -> 27 / 35 / 24;
-// 160^3 41 / 45 / 35 -> 30 / 35 / 23 (2.1 / 2.8 / 2.9 TB/s); 128^3 23 / 22 / 17 ->
-// 16 / 17 / 15; 64^3 16 / 10 / 9 -> 11 / 10 / 9.5; 256^3 divergence 103 -> 96
+// 160^3 41 / 45 / 35 -> 30 / 34 / 23 (2.2 / 2.9 / 2.8 TB/s); 128^3 22 / 23 / 17 ->
+// 15 / 17 / 13; 64^3 15.5 / 8.5 / 9.3 -> 9.2 / 7.6 / 8.9; 256^3 divergence 103 -> 96
 // (4.2 TB/s), absorption 58 -> 59.
 #include "staged_cols.h"
 #include "zstaged.h"

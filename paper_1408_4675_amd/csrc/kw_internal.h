@@ -203,7 +203,7 @@ struct LaunchCfg {
     FftPlan pza, pzai;       // columns per block (the z pass's own unless a
     int tb_za;               // better one is known for its length)
     // x passes on staged transforms (xstaged_impl.h): 0 no, 1 kernels for powers of
-    // two, 2 for any length; which of them (bits XS_*) run so, which on z planes with the
+    // two, 2 for the other lengths; which of them (bits XS_*) run so, which on z planes with the
     // y transforms included; rows of a set in a block, LDS row layout (see pcol)
     int xs;
     unsigned xs_passes, planes;
@@ -211,7 +211,7 @@ struct LaunchCfg {
     int xs_rows[3], xs_pad, xs_pitch, planes_threads[3];
     StageAxis xs_axis, planes_y;
     int zs;                  // z pass on staged transforms (kernels_zs.hip): 0 no, 1 the
-                             // kernels for powers of two, 2 those for any length
+                             // kernels for powers of two, 2 those for the other lengths
     StageAxis zs_axis;
     unsigned zs_skip;        // modes (bit ZM_*) that stay on the engines
     int zs_tb, zs_tb_grad, zs_tb_absm, zs_grad3, zs_threads;  // columns a tile; the gradient's
@@ -304,6 +304,10 @@ hipError_t launch_zfused(hipStream_t s, const GridDev &g, const LaunchCfg &c, co
 hipError_t launch_xvel(hipStream_t s, const GridDev &g, const LaunchCfg &c, const Tables &t,
                        const Medium &m, float2 *const *S, float *const *u,
                        const SourceDev &src, const SensorDev &sen, const Counters &cnt);
+// (three entries in Sout, and in launch_xeos' Sin: the last is a spectrum array that is
+// free, taken as a real scratch field by the pass on staged transforms; the others are the
+// spectra, null where the pass has fewer.  Null will do only without point sensors and
+// pressure sources)
 hipError_t launch_xden(hipStream_t s, const GridDev &g, const LaunchCfg &c, const Tables &t,
                        const Medium &m, const SourceDev &src, const SensorDev &sen,
                        const Counters &cnt, float2 *const *Sin, float *const *rho,

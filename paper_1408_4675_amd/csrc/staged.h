@@ -1,5 +1,5 @@
-// In-place staged transforms in LDS, of any length 2^a 3^b 5^c with up to three
-// stages.
+// In-place staged transforms in LDS, of lengths 2^a 3^b 5^c in up to three stages
+// (columns: every length up to 1024 but 625; x rows: see stage_axis).
 //
 // A transform of n = R0 R1 .. points keeps its natural (frequency) order at
 // one end.  Stage p combines the elements lo + w d + w R hi (w = R0 .. R_{p-1},

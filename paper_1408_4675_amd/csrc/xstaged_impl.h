@@ -1,5 +1,6 @@
-// The x passes of a step on in-place staged transforms (staged.h), for any row
-// length, and with the y transforms around them where a z plane fits LDS.
+// The x passes of a step on in-place staged transforms (staged.h), for the row
+// lengths that have stages (stage_axis), and with the y transforms around them where a z
+// plane fits LDS.
 //
 // A block holds `rows` rows of every field that its update couples: one set of
 // rows for a velocity component, three for the density (the three divergence
@@ -15,13 +16,17 @@
 //
 // What bounds them: on rows vector instructions and barriers (three to four
 // wavefronts a SIMD, five phases a block), on planes the phases of the one or two
-// blocks that a CU holds, which a barrier each keeps in step.  us a launch before (one
-// butterfly a thread; density with its three components exchanged through LDS) and now:
-// 250 x 135 x 90 velocity with its y passes 224 -> 92 (planes; 3.0 M points, 15 fields in
-// and out), density 249 -> 62 (2.6 TB/s), pressure 148 -> 45 (3.3 TB/s); 160^3 velocity
-// with its y passes 127 -> 83 (3.0 TB/s), density 91 -> 86, pressure 60 -> 54; 450 x 480 x
-// 324 density 1686 -> 1309, lossless density with the equation of state 2447 -> 1543;
-// 128^3 velocity with its y passes 51 -> 36.
+// blocks that a CU holds, which a barrier each keeps in step.  us a launch on the engines
+// (one butterfly a thread; density with its three components exchanged through LDS) and
+// here, kernel trace: 250 x 135 x 90 maps, velocity with its y passes 323 -> 90 (planes;
+// 3.0 M points, 15 fields in and out), density 235 -> 54 (2.9 TB/s), pressure 147 -> 42
+// (3.5 TB/s); 160^3 velocity with its y passes 138 -> 83 (3.0 TB/s), density 88 -> 71,
+// pressure 58 -> 53; 450 x 480 x 324 water, velocity 1055 -> 856, density 1550 -> 966,
+// lossless density with the equation of state 2354 -> 1191; 128^3 velocity with its y
+// passes 54 -> 34.
+// Registers: the bounds below keep four wavefronts a SIMD (density three).  Scratch that
+// this costs, bytes a lane: rows, velocity 8, pressure 16 merged and 12-24 unmerged;
+// planes none.
 #pragma once
 
 #include "staged.h"
