@@ -522,7 +522,8 @@ struct AllPoints {
 // waits for a second sweep.  (A second sweep for sensors too, and a wavefront a row in
 // for_points: 64^3 water with point sources and sensors 93 us a step, engines 90, now 76)
 struct PressurePoints {
-    bool source, any;
+    bool source = false, any = false;
+    PressurePoints() = default;
     __device__ __forceinline__ PressurePoints(const XArgs &x, int row0, int ny)
         : source(x.src.kind == KW_SOURCE_PRESSURE && rows_have_points(x.src.row_ptr, row0, ny)),
           any(source || (!x.sen.all_points && rows_have_points(x.sen.row_ptr, row0, ny))) {}
@@ -752,7 +753,8 @@ __global__ void KW_XS_BOUNDS(768, 3) kw_xden_s(XSArgs a) {
     const bool src = x.src.kind == KW_SOURCE_MASS && rows_have_points(x.src.row_ptr, row0, P.rows);
     const int step = *x.cnt.step;
     const bool rec = step >= x.sen.record_start;
-    const PressurePoints pts(x, row0, P.rows);               // (used without absorption)
+    PressurePoints pts;
+    if constexpr (!ABS) pts = PressurePoints(x, row0, P.rows);
     float2 *const out_rho = P.set(sumd ? 1 : 0);
     x_middle<RSM>(a, P, roff, [&](auto RC, const XTask &T, int off, int j) __attribute__((always_inline)) {
         constexpr int R = decltype(RC)::value;
@@ -858,7 +860,8 @@ __global__ void KW_XS_BOUNDS(1024, 4) kw_xeos_s(XSArgs a) {
     to_points<RSY, RSM, RSP, PLANES, MERGED ? 1 : 2>(a, P, [&](int s) __attribute__((always_inline)) { return (s ? x.Sin[1] : x.Sin[0]) + soff; });
     const int step = *x.cnt.step;
     const bool rec = step >= x.sen.record_start;
-    const PressurePoints pts(x, row0, P.rows);
+    PressurePoints pts;
+    if constexpr (POINTS) pts = PressurePoints(x, row0, P.rows);
     x_middle<RSM>(a, P, roff, [&](auto RC, const XTask &T, int off, int j) __attribute__((always_inline)) {
         constexpr int R = decltype(RC)::value;
         float2 p[R], v[R], c[MERGED ? 1 : R];
@@ -883,8 +886,8 @@ __global__ void KW_XS_BOUNDS(1024, 4) kw_xeos_s(XSArgs a) {
                 p[r].y += c[r].y * v[r].y;
             }
         }
-        if (POINTS && pts.any) st_run<R>(a.scr, T, p);
-        if (!POINTS || !pts.source) {
+        if (pts.any) st_run<R>(a.scr, T, p);
+        if (!pts.source) {
             AllPoints{a, step, rec}.template run<R>(T, p);
             run_forward<R>(P, P.sh + off, j, p);
         }
