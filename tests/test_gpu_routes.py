@@ -258,3 +258,29 @@ def test_engines_against_the_oracle(kw, shape, medium, mask):
     print("\n[case] %s" % scen.name, flush=True)
     assert not sim.routes()["staged"]
     _check(sim, scen)
+
+
+@pytest.mark.parametrize("shape", [(64, 64, 6), (100, 90, 4)], ids=["planes", "rows"])
+@pytest.mark.parametrize("kind", [sc.SOURCE_MASS, sc.SOURCE_FORCE, sc.SOURCE_PRESSURE])
+@pytest.mark.parametrize("medium", ["maps", "lossless"])
+def test_points_in_replayed_graphs(kw, shape, kind, medium):
+    """Point sources and sensors in captured graphs, replayed with gathers between, give the
+    bits of launches one by one."""
+    A, Simulation = kw
+    scen = _case(*shape, medium, mask=True)
+    steps = 12
+    rec = sc.REC_P_MAX | sc.REC_P_RMS | sc.REC_P_SERIES | sc.REC_U_SERIES | sc.REC_P_FINAL
+    scen = scen.replace(source=dataclasses.replace(scen.source, kind=kind, amp=scen.source.amp * 0.1),
+                        sensor=dataclasses.replace(scen.sensor, record=rec, series_capacity=steps))
+    print("\n[case] %s kind %d" % (scen.name, kind), flush=True)
+    outs = []
+    for graph_steps in (0, 2):
+        sim = Simulation(scen, tune=False, graph_steps=graph_steps)
+        got = []
+        for _ in range(3):
+            sim.step(steps // 3)
+            got += [sim.gather(w, device=False).ravel() for w in
+                    (A.KW_REC_P_FINAL, A.KW_REC_P_MAX, A.KW_REC_P_RMS, A.KW_REC_P_SERIES, A.KW_REC_U_SERIES)]
+        outs.append(np.concatenate(got))
+        sim.close()
+    assert np.isfinite(outs[0]).all() and np.array_equal(*outs)
