@@ -354,6 +354,21 @@ void pick_zstaged(const GridDev &g, double kx_max, double ky_max, double kz_max,
     // 60 : 71, 1024^3 11400 : 7800; divergence 256^3 95 : 99, 128 x 128 x 512
     // 56 : 74, 1024^3 11600 : 12500
     c.zs_skip = n == 16 * 16 || n == 32 * 32 ? 1u << ZM_GRAD | 1u << ZM_ABSM : 0u;
+    // On spectra beyond the caches the 8- and 12-wide engines keep the passes of one
+    // output a block on the lengths that they transform in a full pass and one of radix 3
+    // or 4 (32, 36, 48).  Staged against fixed, us a launch of divergence / merged
+    // absorption: 512 x 512 x 32 48 : 44 / 49 : 45, 1024 x 512 x 32 105 : 94 / 98 : 89, 1024 x
+    // 768 x 36 246 : 205 / 154 : 148, 640 x 600 x 48 140 : 123 / 100 : 94; spectra of 21 MB, 512
+    // x 320 x 32 35 : 32 / 31 : 23; below 16 MB the staged ones, 256 x 128 x 32 12 : 15 / 15 :
+    // 14, x 48 18 : 21 / 16 : 19.  Neighbours: 1024 x 512 x 24 107 : 118 / 86 : 96, 1024 x 768 x
+    // 64 301 : 376 / 236 : 289; at 72 the gradient outweighs the divergence (the three passes
+    // 974 : 987).  The gradient stays staged (640 x 600 x 48 69 : 75) but at 8 4 from 32 MB
+    // on (512 x 512 x 32 36 : 35, 1024 x 512 x 32 59 : 56; 512 x 256 x 32 24 : 27)
+    const int width = n % 12 == 0 ? 12 : 8;
+    const size_t spectrum = (size_t)g.M * g.ny * n * 8;
+    if ((n == 3 * width || n == 4 * width) && spectrum >= (16u << 20))
+        c.zs_skip |= 1u << ZM_DIV | 1u << ZM_DIVT | 1u << ZM_GRADT | 1u << ZM_ABS | 1u << ZM_ABSM;
+    if (n == 4 * 8 && spectrum >= (32u << 20)) c.zs_skip |= 1u << ZM_GRAD;
     // kappa as a polynomial at every wavenumber of the grid
     const double k2 = kx_max * kx_max + ky_max * ky_max + kz_max * kz_max;
     if ((double)g.half_cdt * g.half_cdt * k2 > kKappaPolyMax) return;

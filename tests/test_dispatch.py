@@ -97,6 +97,10 @@ X = XV | XD | XE
     ((64, 64, 256), "water", [], YF | ZG | ZA, ZD | X, 7),
     ((512, 64, 64), "water", [], YF | YI | XD | XE, ZG | ZD | ZA | XV, 1),
     ((30, 8, 6), "maps", ["set:0::0"], X, YF | YI | ZG | ZD | ZA, 0),
+    # 32 points along z: 32 and 16 MiB of spectrum, and less
+    ((512, 512, 32), "water", [], 255, 0, 0),
+    ((512, 256, 32), "water", [], YF | YI | ZD | ZA | X, ZG, 0),
+    ((512, 128, 32), "water", [], YF | YI | X, ZG | ZD | ZA, 0),
     ((250, 135, 20), "maps", ["set:2::0", "hint:1:9,15:0"], ZG | ZD | ZA, YF | YI | X, 0),
 ])
 def test_routes_name_every_class_once(route, shape, medium, plans, engines, staged, planes):

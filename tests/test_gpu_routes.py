@@ -284,3 +284,25 @@ def test_points_in_replayed_graphs(kw, shape, kind, medium):
         outs.append(np.concatenate(got))
         sim.close()
     assert np.isfinite(outs[0]).all() and np.array_equal(*outs)
+
+
+@pytest.mark.parametrize("shape", [(512, 256, 32), (480, 256, 36), (480, 200, 48)])
+@pytest.mark.parametrize("medium", ["water", "lossless"])
+def test_z_passes_on_both(kw, shape, medium):
+    """Grids whose gradient pass is staged and whose other z passes are not."""
+    A, Simulation = kw
+    scen = _case(*shape, medium)
+    print("\n[case] %s" % scen.name, flush=True)
+    outs = []
+    for forced in (False, True):
+        sim = Simulation(scen, tune=False)
+        if forced:
+            sim.set_plan(2, None)
+        r = sim.routes()
+        assert ("zfused_grad" in r["staged"]) != forced and "zfused_div" in r["engines"]
+        sim.step(STEPS)
+        outs.append([sim.gather(w, device=False) for w in (A.KW_REC_P_FINAL, A.KW_REC_P_MAX)] +
+                    list(sim.gather(A.KW_REC_U_FINAL, device=False).reshape(3, -1)))
+        sim.close()
+    for default, engine in zip(*outs):
+        _same(default, engine)
